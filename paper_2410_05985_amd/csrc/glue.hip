@@ -79,39 +79,77 @@ hipError_t launch_token_sort(const int32_t* tokens, int B, int T, int V, int32_t
   return hipGetLastError();
 }
 
-// dwte[token] += sum over that token's positions (increasing) of dx[pos];
-// one block per sorted slot, active only at the first slot of a token.
-// dwpe[t] = sum over b (increasing) of dx[b, t]: blocks N.. N+T-1.
-__global__ void embed_bwd_kernel(const float* dx, const uint32_t* sorted, float* dwte,
-                                 float* dwpe, int B, int T, int d, int V) {
+// dwte[token] += sum over that token's positions of dx[pos]; one block per
+// (sorted slot, group of 64 float4 columns), active only at the first slot of
+// a token.  dwpe[t] = sum over b of dx[b, t]: slots N.. N+T-1.
+//
+// Text repeats a few tokens hundreds of times (a 2.7 % share of 8192
+// positions is 220 rows), and what bounds the kernel is that longest run:
+// one wave walking it row by row, for every column in turn, took 296 us at
+// 8192 x 768 and 792 us at 8192 x 2048.  So the columns go to separate
+// blocks, EB_WAVES waves take every EB_WAVES-th row of a run, and each wave
+// has EB_UNROLL rows in flight (99 and 122 us).  The order is fixed: a wave's
+// rows in order, then the waves in order, then the head's part.
+constexpr int EB_WAVES = 4;
+constexpr int EB_UNROLL = 8;
+__global__ __launch_bounds__(64 * EB_WAVES) void embed_bwd_kernel(const float* dx, const uint32_t* sorted,
+                                                                  float* dwte, float* dwpe, int B, int T,
+                                                                  int d, int V) {
+  __shared__ f32x4 red[EB_WAVES][64];
   const int n = B * T;
   const int i = blockIdx.x;
-  if (i < n) {
-    const uint32_t tok = sorted[i] >> 14;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int c = blockIdx.y * 64 + lane;
+  const bool on = c < d / 4;
+  const bool wte = i < n;
+  uint32_t tok = 0;
+  if (wte) {
+    tok = sorted[i] >> 14;
     if (tok >= (uint32_t)V) return;
     if (i > 0 && (sorted[i - 1] >> 14) == tok) return;
-    for (int c = threadIdx.x; c < d / 4; c += blockDim.x) {
-      f32x4 acc = reinterpret_cast<const f32x4*>(dwte + (int64_t)tok * d)[c];
-      for (int j = i; j < n && (sorted[j] >> 14) == tok; ++j) {
-        const int pos = sorted[j] & 0x3fff;
-        acc += reinterpret_cast<const f32x4*>(dx + (int64_t)pos * d)[c];
+  }
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  // row k of the run: the position in sorted[i + k], or batch element k
+  const int rows = wte ? n - i : B;
+  for (int k0 = w; k0 < rows; k0 += EB_WAVES * EB_UNROLL) {
+    f32x4 x[EB_UNROLL];
+    bool in = true;
+#pragma unroll
+    for (int u = 0; u < EB_UNROLL; ++u) {
+      const int k = k0 + u * EB_WAVES;
+      int64_t pos = 0;
+      in = k < rows;
+      if (wte) {
+        const uint32_t s = sorted[min(i + k, n - 1)];
+        in = in && (s >> 14) == tok;
+        pos = s & 0x3fff;
+      } else {
+        pos = (int64_t)k * T + (i - n);
       }
-      reinterpret_cast<f32x4*>(dwte + (int64_t)tok * d)[c] = acc;
+      x[u] = in && on ? reinterpret_cast<const f32x4*>(dx + pos * d)[c] : f32x4{0.f, 0.f, 0.f, 0.f};
     }
+#pragma unroll
+    for (int u = 0; u < EB_UNROLL; ++u) acc += x[u];
+    if (!in) break;  // the run ended inside this group of rows
+  }
+  red[w][lane] = acc;
+  __syncthreads();
+  if (w > 0 || !on) return;
+#pragma unroll
+  for (int k = 1; k < EB_WAVES; ++k) acc += red[k][lane];
+  if (wte) {
+    f32x4* o = reinterpret_cast<f32x4*>(dwte + (int64_t)tok * d) + c;
+    *o = *o + acc;
   } else {
-    const int t = i - n;
-    for (int c = threadIdx.x; c < d / 4; c += blockDim.x) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      for (int b = 0; b < B; ++b) acc += reinterpret_cast<const f32x4*>(dx + ((int64_t)b * T + t) * d)[c];
-      reinterpret_cast<f32x4*>(dwpe + (int64_t)t * d)[c] = acc;
-    }
+    reinterpret_cast<f32x4*>(dwpe + (int64_t)(i - n) * d)[c] = acc;
   }
 }
 
 hipError_t launch_embed_bwd(const float* dx, const int32_t* sorted_pos, float* dwte, float* dwpe,
                             int B, int T, int d, int V, hipStream_t s) {
-  embed_bwd_kernel<<<B * T + T, 64, 0, s>>>(dx, reinterpret_cast<const uint32_t*>(sorted_pos), dwte,
-                                            dwpe, B, T, d, V);
+  const dim3 grid((unsigned)(B * T + T), (unsigned)cdiv(d / 4, 64));
+  embed_bwd_kernel<<<grid, 64 * EB_WAVES, 0, s>>>(dx, reinterpret_cast<const uint32_t*>(sorted_pos), dwte,
+                                                  dwpe, B, T, d, V);
   return hipGetLastError();
 }
 

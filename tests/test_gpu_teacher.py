@@ -129,3 +129,43 @@ def test_update_mix_teacher_forced_two_steps(cfg):
         m0 = {k: a.astype(np.float64) for k, a in got_m.items()}
         v0 = {k: a.astype(np.float64) for k, a in got_v.items()}
     m.close()
+
+
+def test_embedding_backward_long_runs():
+    """Runs of one token at the edges of the scatter's grouping (4 waves of 8
+    rows in flight): 1, 31, 32, 33 and 700 positions of one token, the rest
+    drawn, and tokens outside the vocabulary (no row).  dwte = the head's
+    part + the run's rows, dwpe = the sum over the batch: float32 sums of at
+    most 701 terms in any order, each within 701 * 2^-24 (1.01 for higher
+    orders) of the exact sum times the sum of absolute values."""
+    cfg = S.GPT_TEST_LONG
+    params, tokens, peers, m = gpt_setup(cfg)
+    hp, _ = gpt_hp(cfg)
+    N, d, V, T = cfg.batch * cfg.seq, cfg.d_model, cfg.vocab, cfg.seq
+    rng = np.random.default_rng(11)
+    flat = rng.integers(20, V, N).astype(np.int32)
+    at = 0
+    for tok, n in ((3, 1), (4, 31), (5, 32), (6, 33), (7, 700), (-1, 5), (V, 6)):
+        flat[at:at + n] = tok
+        at += n
+    tokens = np.concatenate([rng.permutation(flat).reshape(cfg.batch, T), tokens[:, -1:]], axis=1).astype(np.int32)
+    td = torch.from_numpy(np.ascontiguousarray(tokens)).to(DEV)
+    torch.cuda.synchronize()
+    LU.layup_forward(m.ctx, td, None, None)
+    for u in range(cfg.n_layer + 1, 0, -1):
+        LU.layup_layer_backward(m.ctx, u)
+        LU.layup_unit_update_mix(m.ctx, u, hp, cfg.alpha, 0)
+    head = m.read("grads")["wte"].astype(np.float64)
+    dx = m.activation(13).astype(np.float64).reshape(cfg.batch, T, d)
+    LU.layup_layer_backward(m.ctx, 0)
+    LU.layup_unit_update_mix(m.ctx, 0, hp, cfg.alpha, 0)
+    got = m.read("grads")
+    ids = tokens[:, :T]
+    ok = (ids >= 0) & (ids < V)
+    ref, mag = head.copy(), np.abs(head)
+    np.add.at(ref, ids[ok], dx[ok])
+    np.add.at(mag, ids[ok], np.abs(dx[ok]))
+    eps = 1.01 * 701 * 2.0 ** -24
+    assert np.all(np.abs(got["wte"] - ref) <= eps * mag)
+    assert np.all(np.abs(got["wpe"] - dx.sum(0)) <= eps * np.abs(dx).sum(0))
+    m.close()
