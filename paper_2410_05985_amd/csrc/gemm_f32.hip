@@ -1,88 +1,194 @@
-// float32 GEMM for the float32 MLP workload (batch 32, widths <= 512): the
-// products are a few MFLOP, so the kernel is latency-bound and kept simple:
-// 64x64 block tiles staged through LDS, 4x4 outputs per thread, plain FMA.
+// float32 GEMM of the float32 MLP on the float32 matrix instructions
+// (v_mfma_f32_16x16x4_f32: full float32 products and sums).
+//
+// The MLP's products are a few MFLOP (32 x 256 x 512), so what bounds them is
+// the chain of dependent memory round trips along K, not arithmetic: 64 x 64
+// tiles put 32 x 256 x 512 on 4 workgroups that walked K in 32 barrier steps
+// (48 us).  Here a workgroup owns a small output tile and its NW waves split
+// K between them: each wave loads its operand fragments straight from global
+// memory into registers, four 16-deep K chunks in flight, and the waves'
+// partial tiles are added through LDS in wave order (deterministic).  No LDS
+// staging: an operand element is read by one tile row or column, from L2.
 #include "layup_internal.h"
 
 namespace layup {
 
 namespace {
-constexpr int TB = 64, TK = 16;
 
-template <bool AK, bool BKM>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A,
-                                                       const float* __restrict__ B, float* C,
-                                                       const float* bias, const float* aux,
-                                                       int64_t M, int64_t N, int64_t K,
-                                                       int64_t lda, int64_t ldb, int64_t ldc) {
-  __shared__ float sA[TK][TB + 4];
-  __shared__ float sB[TK][TB + 4];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int64_t m0 = (int64_t)blockIdx.y * TB, n0 = (int64_t)blockIdx.x * TB;
-  float acc[4][4] = {};
-  for (int64_t k0 = 0; k0 < K; k0 += TK) {
-    for (int e = threadIdx.x; e < TK * TB; e += 256) {
-      int kk, r;
-      if (AK) { r = e / TK; kk = e % TK; } else { kk = e / TB; r = e % TB; }
-      int64_t gm = m0 + r, gk = k0 + kk;
-      float va = 0.f;
-      if (gm < M && gk < K) va = AK ? A[gm * lda + gk] : A[gk * lda + gm];
-      sA[kk][r] = va;
-      if (BKM) { r = e / TK; kk = e % TK; } else { kk = e / TB; r = e % TB; }
-      int64_t gn = n0 + r;
-      gk = k0 + kk;
-      float vb = 0.f;
-      if (gn < N && gk < K) vb = BKM ? B[gn * ldb + gk] : B[gk * ldb + gn];
-      sB[kk][r] = vb;
-    }
-    __syncthreads();
+struct F32Args {
+  const float* A;
+  const float* B;
+  float* C;
+  const float* bias;
+  const float* aux;
+  const float* mask;
+  float* rowsum;
+  int64_t M, N, K, lda, ldb, ldc;
+  int32_t relu, vec_a, vec_b;
+};
+
+// Four consecutive k (k0..k0+3) of row r of an operand, zero past K.
+// k-major: element (r, k) at p[r*ld + k]; m-major: at p[k*ld + r].
+template <bool KMAJOR>
+__device__ __forceinline__ f32x4 load4(const float* p, int64_t ld, int64_t r, int64_t k0, int64_t K, bool vec) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (KMAJOR && vec && k0 + 4 <= K) return *reinterpret_cast<const f32x4*>(p + r * ld + k0);
 #pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      float a[4], b[4];
+  for (int e = 0; e < 4; ++e)
+    if (k0 + e < K) v[e] = KMAJOR ? p[r * ld + k0 + e] : p[(k0 + e) * ld + r];
+  return v;
+}
+
+// T x T blocks of 16 x 16 outputs per workgroup; wave w takes the K chunks
+// w, w + NW, ... of 16.  Fragment layout: lane l holds row (column) l % 16 and
+// the four k of group l / 16; instruction e multiplies the k 4 g + e of the
+// four groups g, the same set for both operands.
+template <bool AK, bool BKM, int T, int NW>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const F32Args P) {
+  constexpr int UN = T == 1 ? 4 : 2;  // K chunks in flight
+  __shared__ float red[NW > 1 ? NW : 1][T * T][4][64];
+  __shared__ float rred[NW][T][16];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int g = lane >> 4, r16 = lane & 15;
+  const int64_t m0 = (int64_t)blockIdx.y * (16 * T), n0 = (int64_t)blockIdx.x * (16 * T);
+  int64_t ar[T], br[T];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sA[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = sB[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+  for (int i = 0; i < T; ++i) {
+    ar[i] = min(m0 + 16 * i + r16, P.M - 1);
+    br[i] = min(n0 + 16 * i + r16, P.N - 1);
   }
+  f32x4 acc[T][T];
+  float rs[T];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int64_t m = m0 + ty * 4 + i;
-    if (m >= M) continue;
+  for (int i = 0; i < T; ++i) {
+    rs[i] = 0.f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int64_t n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      float v = acc[i][j];
-      if (bias) v += bias[n];
-      if (aux) v += aux[m * ldc + n];
-      C[m * ldc + n] = v;
+    for (int j = 0; j < T; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int64_t c0 = 16 * w; c0 < P.K; c0 += 16 * NW * UN) {
+    f32x4 a[UN][T], b[UN][T];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int64_t k = c0 + (int64_t)16 * NW * u + 4 * g;
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        a[u][i] = load4<AK>(P.A, P.lda, ar[i], k, P.K, P.vec_a);
+        b[u][i] = load4<BKM>(P.B, P.ldb, br[i], k, P.K, P.vec_b);
+      }
     }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+          for (int j = 0; j < T; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][e], b[u][j][e], acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < T; ++i) rs[i] += (a[u][i][0] + a[u][i][1]) + (a[u][i][2] + a[u][i][3]);
+    }
+  }
+  const bool rowsum = P.rowsum && blockIdx.x == 0;
+  if (rowsum) {
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+      float s = rs[i] + __shfl_xor(rs[i], 16, 64);
+      s += __shfl_xor(s, 32, 64);
+      if (lane < 16) rred[w][i][lane] = s;
+    }
+  }
+  if (NW > 1) {
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+      for (int j = 0; j < T; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) red[w][i * T + j][e][lane] = acc[i][j][e];
+  }
+  __syncthreads();
+  if (rowsum) {
+    for (int x = threadIdx.x; x < 16 * T; x += 64 * NW) {
+      float s = rred[0][x / 16][x % 16];
+      for (int k = 1; k < NW; ++k) s += rred[k][x / 16][x % 16];
+      if (m0 + x < P.M) P.rowsum[m0 + x] = s;
+    }
+  }
+  // wave w finishes output registers w, w + NW, ... of the tile's T*T*4
+#pragma unroll
+  for (int x = 0; x < T * T * 4; ++x) {
+    if (x % NW != w) continue;
+    const int blk = x / 4, e = x % 4;
+    float v = NW > 1 ? red[0][blk][e][lane] : acc[blk / T][blk % T][e];
+    if (NW > 1)
+      for (int k = 1; k < NW; ++k) v += red[k][blk][e][lane];
+    const int64_t m = m0 + 16 * (blk / T) + 4 * g + e, n = n0 + 16 * (blk % T) + r16;
+    if (m >= P.M || n >= P.N) continue;
+    const int64_t off = m * P.ldc + n;
+    if (P.bias) v += P.bias[n];
+    if (P.aux) v += P.aux[off];
+    if (P.relu) v = v > 0.f ? v : 0.f;
+    if (P.mask) v = P.mask[off] > 0.f ? v : 0.f;
+    P.C[off] = v;
   }
 }
+
+template <int T, int NW>
+hipError_t launch_tile(const Gemm& g, const F32Args& P, hipStream_t s) {
+  const int64_t gy = cdiv(P.M, 16 * T);
+  // grid.y holds 65535 row tiles: taller products go in bands of rows
+  constexpr int64_t BAND = 65535;
+  for (int64_t y = 0; y < gy; y += BAND) {
+    F32Args Q = P;
+    const int64_t r0 = y * 16 * T;
+    Q.M = std::min<int64_t>(P.M - r0, BAND * 16 * T);
+    if (Q.A) Q.A += g.a_kmajor ? r0 * P.lda : r0;
+    Q.C += r0 * P.ldc;
+    if (Q.aux) Q.aux += r0 * P.ldc;
+    if (Q.mask) Q.mask += r0 * P.ldc;
+    if (Q.rowsum) Q.rowsum += r0;
+    // a band's first row keeps the vector loads' alignment (k-major: lda a
+    // multiple of 4; m-major operands are read element by element)
+    const dim3 grid((unsigned)cdiv(P.N, 16 * T), (unsigned)cdiv(Q.M, 16 * T));
+    if (g.a_kmajor && g.b_kmajor) gemm_f32_kernel<true, true, T, NW><<<grid, 64 * NW, 0, s>>>(Q);
+    else if (g.a_kmajor) gemm_f32_kernel<true, false, T, NW><<<grid, 64 * NW, 0, s>>>(Q);
+    else if (g.b_kmajor) gemm_f32_kernel<false, true, T, NW><<<grid, 64 * NW, 0, s>>>(Q);
+    else gemm_f32_kernel<false, false, T, NW><<<grid, 64 * NW, 0, s>>>(Q);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 }  // namespace
 
 hipError_t launch_gemm_f32(const Gemm& g, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return hipSuccess;
   if (g.batch != 1) return hipErrorInvalidValue;
-  dim3 grid((unsigned)cdiv(g.N, TB), (unsigned)cdiv(g.M, TB));
-  const float* A = (const float*)g.A;
-  const float* B = (const float*)g.B;
-  float* C = (float*)g.C;
-  const float* aux = (const float*)g.aux;
-#define LAUNCH(ak, bk)                                                                         \
-  gemm_f32_kernel<ak, bk><<<grid, 256, 0, s>>>(A, B, C, g.bias, aux, g.M, g.N, g.K, g.lda, \
-                                               g.ldb, g.ldc)
-  if (g.a_kmajor && g.b_kmajor) LAUNCH(true, true);
-  else if (g.a_kmajor) LAUNCH(true, false);
-  else if (g.b_kmajor) LAUNCH(false, true);
-  else LAUNCH(false, false);
-#undef LAUNCH
-  return hipGetLastError();
+  F32Args P;
+  P.A = (const float*)g.A;
+  P.B = (const float*)g.B;
+  P.C = (float*)g.C;
+  P.bias = g.bias;
+  P.aux = (const float*)g.aux;
+  P.mask = g.mask;
+  P.rowsum = g.rowsum;
+  P.M = g.M;
+  P.N = g.N;
+  P.K = g.K;
+  P.lda = g.lda;
+  P.ldb = g.ldb;
+  P.ldc = g.ldc;
+  P.relu = g.relu;
+  P.vec_a = g.lda % 4 == 0 && ((uintptr_t)g.A & 15) == 0;
+  P.vec_b = g.ldb % 4 == 0 && ((uintptr_t)g.B & 15) == 0;
+  // 16 x 16 tiles while they do not fill the chip a few times over (each of
+  // the 256 CUs holds four 8-wave workgroups); beyond that 32 x 32 tiles read
+  // each operand half as often.  Eight waves where K gives each of them more
+  // than one chunk, two for the short K of dW (the batch).
+  const int64_t t16 = cdiv(g.M, 16) * cdiv(g.N, 16);
+  if (t16 > 4096) return g.K > 64 ? launch_tile<2, 4>(g, P, s) : launch_tile<2, 1>(g, P, s);
+  return g.K > 64 ? launch_tile<1, 8>(g, P, s) : launch_tile<1, 2>(g, P, s);
 }
 
 }  // namespace layup

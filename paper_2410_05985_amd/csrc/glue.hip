@@ -1,6 +1,6 @@
 // Non-GEMM kernels of the GPT and MLP forward/backward: embedding gather and
-// deterministic scatter, LayerNorm, causal softmax, cross-entropy, column
-// sums (bias gradients), conversions.  All are HBM-bound elementwise or
+// deterministic scatter, LayerNorm, causal softmax, cross-entropy,
+// conversions.  All are HBM-bound elementwise or
 // row-reduction kernels; math is float32 in registers, storage as the caller
 // chooses (bf16 activations, f32 residual stream and gradients).  Every
 // reduction has a fixed order, so results are bitwise reproducible.
@@ -457,125 +457,6 @@ hipError_t launch_layernorm_bwd(const float* dy, const float* x, const float* me
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------ column sums
-// out[c] = sum over rows of x[r*ld + c] in a fixed order: stage 1 sums
-// chunks of CS_ROWS rows (inside a chunk: rows r = l, l+8, ... per row lane
-// l, then the 8 row lanes in order) into partial rows, stage 2 sums the
-// partial rows in chunk order.  Stage 1 reads 16 bytes per thread per row,
-// coalesced across the 32 column groups of a block.  Columns >= split go to
-// out2[c - split] when out2 is given.
-constexpr int CS_ROWS = 128;
-
-template <typename T>
-__device__ __forceinline__ void load_vec(const T* p, float* out);
-template <>
-__device__ __forceinline__ void load_vec<bf16_t>(const bf16_t* p, float* out) {
-  const u32x4 v = *reinterpret_cast<const u32x4*>(p);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    out[2 * i] = __builtin_bit_cast(float, v[i] << 16);
-    out[2 * i + 1] = __builtin_bit_cast(float, v[i] & 0xffff0000u);
-  }
-}
-template <>
-__device__ __forceinline__ void load_vec<float>(const float* p, float* out) {
-  const f32x4 v = *reinterpret_cast<const f32x4*>(p);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) out[i] = v[i];
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void colsum_stage1(const T* x, int64_t rows, int64_t cols, int64_t ld,
-                                                     float* partial) {
-  constexpr int VEC = 16 / sizeof(T);
-  __shared__ float red[8][32 * VEC];
-  const int cg = threadIdx.x & 31, rl = threadIdx.x >> 5;
-  const int64_t c0 = ((int64_t)blockIdx.x * 32 + cg) * VEC;
-  const int64_t r0 = (int64_t)blockIdx.y * CS_ROWS;
-  const int64_t r1 = min(rows, r0 + CS_ROWS);
-  float acc[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
-  if (c0 < cols) {
-    for (int64_t r = r0 + rl; r < r1; r += 8) {
-      float v[VEC];
-      load_vec<T>(x + r * ld + c0, v);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) acc[e] += v[e];
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) red[rl][cg * VEC + e] = acc[e];
-  __syncthreads();
-  for (int i = threadIdx.x; i < 32 * VEC; i += 256) {
-    const int64_t c = (int64_t)blockIdx.x * 32 * VEC + i;
-    if (c >= cols) continue;
-    float t = red[0][i];
-    for (int l = 1; l < 8; ++l) t += red[l][i];
-    partial[(int64_t)blockIdx.y * cols + c] = t;
-  }
-}
-
-// Scalar stage 1 for narrow or unaligned inputs (the float32 MLP's 10 classes).
-template <typename T>
-__global__ void colsum_scalar(const T* x, int64_t rows, int64_t cols, int64_t ld, float* partial) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= cols) return;
-  const int64_t r0 = (int64_t)blockIdx.y * CS_ROWS;
-  const int64_t r1 = min(rows, r0 + CS_ROWS);
-  float s = 0.f;
-  for (int64_t r = r0; r < r1; ++r) {
-    if constexpr (sizeof(T) == 2) s += bf2f(x[r * ld + c]);
-    else s += x[r * ld + c];
-  }
-  partial[(int64_t)blockIdx.y * cols + c] = s;
-}
-
-// 64 columns x 4 chunk lanes per block: lane l sums chunks l, l+4, ... in
-// order, then the four lane sums are added in lane order.
-__global__ __launch_bounds__(256) void colsum_final_kernel(const float* partial, int64_t chunks,
-                                                           int64_t cols, float* out, float* out2,
-                                                           int64_t split) {
-  __shared__ float red[4][64];
-  const int cl = threadIdx.x & 63, l = threadIdx.x >> 6;
-  const int64_t c = (int64_t)blockIdx.x * 64 + cl;
-  float s = 0.f;
-  if (c < cols)
-    for (int64_t k = l; k < chunks; k += 4) s += partial[k * cols + c];
-  red[l][cl] = s;
-  __syncthreads();
-  if (l == 0 && c < cols) {
-    const float t = (red[0][cl] + red[1][cl]) + (red[2][cl] + red[3][cl]);
-    if (out2 && c >= split) out2[c - split] = t;
-    else out[c] = t;
-  }
-}
-
-template <typename T>
-hipError_t colsum2(const T* x, int64_t rows, int64_t cols, int64_t ld, const ColsumScratch& cs,
-                   float* out, float* out2, int64_t split, hipStream_t s) {
-  constexpr int VEC = 16 / sizeof(T);
-  const int64_t chunks = cdiv(rows, CS_ROWS);
-  if (chunks > 65535 || chunks * cols > cs.partial_floats) return hipErrorInvalidValue;
-  const bool vec = cols % VEC == 0 && ld % VEC == 0 && ((uintptr_t)x & 15) == 0;
-  if (vec) {
-    dim3 g1((unsigned)cdiv(cols, 32 * VEC), (unsigned)chunks);
-    colsum_stage1<T><<<g1, 256, 0, s>>>(x, rows, cols, ld, cs.partial);
-  } else {
-    dim3 g1((unsigned)cdiv(cols, 256), (unsigned)chunks);
-    colsum_scalar<T><<<g1, 256, 0, s>>>(x, rows, cols, ld, cs.partial);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  colsum_final_kernel<<<(unsigned)cdiv(cols, 64), 256, 0, s>>>(cs.partial, chunks, cols, out, out2, split);
-  return hipGetLastError();
-}
-
-hipError_t launch_colsum_f32(const float* x, int64_t rows, int64_t cols, int64_t ld,
-                             const ColsumScratch& cs, float* out, hipStream_t s) {
-  return colsum2<float>(x, rows, cols, ld, cs, out, nullptr, 0, s);
-}
-
 // ------------------------------------------------------- causal softmax
 // P[i, j] = exp(scale*S[i,j] - max) / sum for j <= i, 0 for j > i.  One wave64
 // per row; 16-byte loads of S; only the unmasked part of S is read.
@@ -945,26 +826,6 @@ hipError_t launch_f32_to_bf16(const float* x, bf16_t* y, int64_t n, hipStream_t 
   if (n == 0) return hipSuccess;
   unsigned blocks = (unsigned)std::min<int64_t>(cdiv(n / 4 + 1, 256), 8192);
   f32_to_bf16_kernel<<<blocks, 256, 0, s>>>(x, y, n);
-  return hipGetLastError();
-}
-
-__global__ void relu_kernel(float* x, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    x[i] = x[i] > 0.f ? x[i] : 0.f;
-}
-
-__global__ void relu_bwd_kernel(float* dy, const float* y, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    dy[i] = y[i] > 0.f ? dy[i] : 0.f;
-}
-
-hipError_t launch_relu_inplace(float* x, int64_t n, hipStream_t s) {
-  relu_kernel<<<(unsigned)std::min<int64_t>(cdiv(n, 256), 4096), 256, 0, s>>>(x, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_relu_bwd_inplace(float* dy, const float* y, int64_t n, hipStream_t s) {
-  relu_bwd_kernel<<<(unsigned)std::min<int64_t>(cdiv(n, 256), 4096), 256, 0, s>>>(dy, y, n);
   return hipGetLastError();
 }
 

@@ -157,6 +157,10 @@ struct Gemm {
   // m-major A only (dW = dY^T X): rowsum[m] = sum over k of A(m, k), the
   // bias gradient, accumulated from the A fragments the MFMAs consume
   float* rowsum = nullptr;
+  // float32 path only, applied after bias and aux: the ReLU of the result,
+  // and its gradient (zero where mask <= 0; mask laid out as C)
+  int relu = 0;
+  const float* mask = nullptr;
 };
 enum Causal : int { CAUSAL_NONE = 0, CAUSAL_OUT_LOWER = 1, CAUSAL_A_LOWER = 2, CAUSAL_A_UPPER = 3 };
 
@@ -173,11 +177,6 @@ hipError_t launch_embed_fwd(const int32_t* tokens, const float* wte, const float
                             int B, int T, int d, int V, hipStream_t s);
 hipError_t launch_layernorm_fwd(const float* x, const float* g, const float* b, bf16_t* y,
                                 float* mean, float* rstd, int64_t rows, int d, hipStream_t s);
-// Scratch of the column sums: partial rows, ceil(rows/128) x cols floats.
-struct ColsumScratch {
-  float* partial;
-  int64_t partial_floats;
-};
 // LayerNorm backward: dx (float32) and optionally its bfloat16 copy dx16;
 // per-block partial sums of dg and db go to part
 // (layernorm_bwd_partial_floats(rows, d) floats) and are added into dg, db
@@ -212,15 +211,11 @@ hipError_t launch_ce_fwd_bwd(const bf16_t* logits, int64_t ld, const int32_t* to
                              hipStream_t s, int64_t mean_rows = 0);
 hipError_t launch_row_mean(const float* x, int64_t n, float* out, hipStream_t s);
 hipError_t launch_f32_to_bf16(const float* x, bf16_t* y, int64_t n, hipStream_t s);
-hipError_t launch_colsum_f32(const float* x, int64_t rows, int64_t cols, int64_t ld,
-                             const ColsumScratch& cs, float* out, hipStream_t s);
 hipError_t launch_embed_bwd(const float* dx, const int32_t* sorted_pos, float* dwte, float* dwpe,
                             int B, int T, int d, int V, hipStream_t s);
 hipError_t launch_token_sort(const int32_t* tokens, int B, int T, int V, int32_t* counts,
                              int32_t* sorted_pos, int32_t* seg_start, int32_t* seg_token,
                              int32_t* n_seg, hipStream_t s);
-hipError_t launch_relu_bwd_inplace(float* dy, const float* y, int64_t n, hipStream_t s);
-hipError_t launch_relu_inplace(float* x, int64_t n, hipStream_t s);
 hipError_t launch_ce_f32(const float* logits, const int32_t* labels, int rows, int V,
                          float* dlogits, float* loss_rows, float* loss_out, hipStream_t s);
 

@@ -206,9 +206,7 @@ struct layup_ctx {
   hipEvent_t ev_sort = nullptr;  // the token sort done (update stream)
   hipEvent_t ev_fwd_half = nullptr;  // the forward's second half done (update stream)
   bool unit_recorded = false;  // the backward recorded its unit event itself
-  float *ln_part = nullptr, *cs_part = nullptr;
-  int64_t cs_part_floats = 0;
-  ColsumScratch cs() const { return ColsumScratch{cs_part, cs_part_floats}; }
+  float* ln_part = nullptr;
   float *splitk = nullptr, *splitk_su = nullptr;
   size_t splitk_bytes = 0, splitk_su_bytes = 0;
   bool dw_side() const { return su != sc; }
@@ -287,8 +285,6 @@ size_t carve(layup_ctx* c, char* base) {
     c->mlp_dz = cv.take<float>(g.batch * wmax);
     c->mlp_dh = cv.take<float>(g.batch * wmax);
     c->loss_rows = cv.take<float>(g.batch);
-    c->cs_part_floats = cdiv(g.batch, 128) * wmax;
-    c->cs_part = cv.take<float>(c->cs_part_floats);
   }
   c->dis_partial = cv.take<float>(UM_MAX_BLOCKS);
   return cv.used + 256;
@@ -699,8 +695,8 @@ layup_status mlp_forward(layup_ctx* c, const int32_t* labels, const float* x, fl
     const int in = g.mlp_dims[i], out = g.mlp_dims[i + 1];
     Gemm gm = mk(true, true, Bt, out, in, h, in, fl.p(p + "w"), in, c->mlp_act[i + 1], out, EPI_F32);
     gm.bias = fl.p(p + "b");
+    gm.relu = i + 1 < n;
     TRY(mlp_gemm(c, gm, "mlp forward"));
-    if (i + 1 < n) HIPCHK(c, launch_relu_inplace(c->mlp_act[i + 1], (int64_t)Bt * out, c->sc), "relu");
     h = c->mlp_act[i + 1];
   }
   HIPCHK(c, launch_ce_f32(c->mlp_act[n], labels, Bt, g.mlp_dims[n], c->mlp_dz, c->loss_rows, loss_out,
@@ -714,13 +710,14 @@ layup_status mlp_backward(layup_ctx* c, int u) {
   Flat fl{c};
   const std::string p = "fc" + std::to_string(u + 1) + ".";
   const float* hin = u == 0 ? c->mlp_x : c->mlp_act[u];
-  TRY(mlp_gemm(c, mk(false, false, out, in, Bt, c->mlp_dz, out, hin, in, fl.g(p + "w"), in, EPI_F32),
-               "mlp dW"));
-  HIPCHK(c, launch_colsum_f32(c->mlp_dz, Bt, out, out, c->cs(), fl.g(p + "b"), c->sc), "mlp db");
+  // db (column sums of dz) comes out of the dW product, the ReLU's gradient out of dX
+  Gemm dw = mk(false, false, out, in, Bt, c->mlp_dz, out, hin, in, fl.g(p + "w"), in, EPI_F32);
+  dw.rowsum = fl.g(p + "b");
+  TRY(mlp_gemm(c, dw, "mlp dW + db"));
   if (u > 0) {
-    TRY(mlp_gemm(c, mk(true, false, Bt, in, out, c->mlp_dz, out, fl.p(p + "w"), in, c->mlp_dh, in,
-                       EPI_F32), "mlp dX"));
-    HIPCHK(c, launch_relu_bwd_inplace(c->mlp_dh, c->mlp_act[u], (int64_t)Bt * in, c->sc), "relu bwd");
+    Gemm dx = mk(true, false, Bt, in, out, c->mlp_dz, out, fl.p(p + "w"), in, c->mlp_dh, in, EPI_F32);
+    dx.mask = c->mlp_act[u];
+    TRY(mlp_gemm(c, dx, "mlp dX"));
     std::swap(c->mlp_dz, c->mlp_dh);
   }
   return LAYUP_OK;

@@ -248,3 +248,26 @@ def test_gemm_f32(layout):
     LU.layup_gemm_f32(d, torch.cuda.current_stream())
     torch.cuda.synchronize()
     compare(Cd.cpu().numpy(), ref, 1e-5, "f32 gemm")
+
+
+@pytest.mark.parametrize("ak,bk", [(True, True), (True, False), (False, False), (False, True)])
+@pytest.mark.parametrize("M,N,K,ld", [(1, 1, 1, 0), (16, 16, 64, 0), (17, 33, 65, 0), (31, 15, 513, 3), (64, 48, 515, 4),
+                                      (1040, 1000, 20, 1), (1100, 1010, 70, 0)])
+def test_gemm_f32_tiles_and_remainders(ak, bk, M, N, K, ld):
+    """Edges of the 16 x 16 and 32 x 32 tiles, of the K chunks of each wave
+    and of the vector loads (leading dimensions off a multiple of four).
+    Bound: a float32 sum of K products in any order is within (K + 1) 2^-24
+    (first order; 1.01 for the rest) of the exact one, times the sum of
+    their absolute values."""
+    g = torch.Generator().manual_seed(M + 7 * N + 13 * K)
+    A = torch.randn((M, K + ld) if ak else (K, M + ld), generator=g)
+    B = torch.randn((N, K + ld) if bk else (K, N + ld), generator=g)
+    a = (A[:, :K] if ak else A[:, :M].t()).double()
+    b = (B[:, :K].t() if bk else B[:, :N]).double()
+    Ad, Bd = A.to(DEV), B.to(DEV)
+    C = torch.full((M, N), float("nan"), device=DEV)
+    LU.layup_gemm_f32(LU.gemm_desc(Ad, Bd, C, M, N, K, A.shape[1], B.shape[1], N, ak, bk, True),
+                      torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    bound = 1.01 * (K + 1) * 2.0 ** -24 * (a.abs() @ b.abs())
+    assert torch.all((C.cpu().double() - a @ b).abs() <= bound)
