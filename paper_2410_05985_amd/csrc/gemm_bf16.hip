@@ -6,7 +6,7 @@
 //
 // Structure: a BM x BN block tile computed by a WGM x WGN grid of wave64s,
 // each wave a (BM/WGM) x (BN/WGN) tile of 32x32 MFMA blocks with float32
-// accumulators in registers.  K advances in steps of 32 through a ring of LDS
+// accumulators in registers.  K advances in steps of 32 or 64 through a ring of LDS
 // stages filled by direct-to-LDS loads (see the pipeline notes below), so
 // several K steps of both operands are in flight while one is multiplied and
 // no registers stage the copy.  An operand that is k-contiguous in HBM stays
@@ -175,15 +175,14 @@ __device__ __forceinline__ void epi_store(const KArgs& P, int split, int64_t c_o
 }
 
 // ------------------------------------------------------------ pipeline
-// K advances in steps of BKV (32 or 64) through rings of LDS stages (one for
-// the A tiles, one for the B tiles; A may run one stage deeper).  Every
+// K advances in steps of BKV (32 or 64) through rings of LDS stages.  Every
 // operand tile is copied HBM -> LDS by direct-to-LDS loads
 // (global_load_lds_dwordx4: each lane's 16 bytes land at LDS base + 16*lane,
 // one 1 KB block per wave instruction), so no registers stage the data and
-// the tiles of the next stages are in flight while one is multiplied.  Addresses are clamped
-// into the operand (rows >= R read row R-1, k past the end reads the last
-// chunk); rows beyond R only feed discarded outputs and the k tail of the last
-// tile is zeroed in LDS before use.
+// the tiles of the next stages are in flight while one is multiplied.  Rows
+// are clamped into the operand (rows >= R read row R-1: they only feed
+// discarded outputs); the last, partial K step also clamps k, and its tail is
+// zeroed in LDS before use.
 //
 // LDS layouts (per tile, byte offsets):
 //  k-major operand, ROWS x 32: row r = 64 B = four 16-byte chunks; chunk c at
@@ -247,6 +246,34 @@ __device__ __forceinline__ void issue_block(const bf16_t* base, int64_t ld, int6
     }
     __builtin_amdgcn_global_load_lds(src, LDS_PTR(lds + blk * 1024), 16, 0, 0);
   }
+}
+
+// Where this lane's 16 bytes of copy i of a wave's share come from, for the
+// whole K steps from k0 on (rows clamped as above, k in range): the next
+// step's are a fixed number of bytes further.
+template <int ROWS, bool KMAJOR, int BKV, int NWAVES>
+__device__ __forceinline__ const char* block_src(const bf16_t* base, int64_t ld, int64_t r0, int64_t k0,
+                                                 int64_t R, int wave, int lane, int i) {
+  const int blk = wave * (ROWS * BKV * 2 / 1024 / NWAVES) + i;
+  if (KMAJOR) {
+    constexpr int KCH = BKV / 8;
+    const int row = blk * (64 / KCH) + lane / KCH;
+    const int c = (lane % KCH) ^ kswz(row, BKV);
+    return reinterpret_cast<const char*>(base + min(r0 + row, R - 1) * ld + k0 + 8 * c);
+  } else {
+    constexpr int LPR = ROWS / 8;
+    const int q = blk * 64 + lane;
+    const int kk = q / LPR;
+    const int c = (q % LPR) ^ mm_sw<ROWS>(kk);
+    return reinterpret_cast<const char*>(base + (k0 + kk) * ld + min(r0 + 8 * c, R - 8));
+  }
+}
+
+// One 1 KB block, 16 bytes per lane.  (A function template: the builtin's
+// width is checked against the target, and the host pass has none.)
+template <int>
+__device__ __forceinline__ void copy_block(const char* src, char* lds) {
+  __builtin_amdgcn_global_load_lds(src, LDS_PTR(lds), 16, 0, 0);
 }
 
 // Zero the k >= krem part of a tile (last, partial K step).
@@ -357,28 +384,25 @@ __device__ __forceinline__ void barrier_only() {
 }
 
 // WGM x WGN waves per workgroup; each wave owns a (BM/WGM) x (BN/WGN) block of
-// 32x32 MFMA tiles.  More waves issue more direct-to-LDS copies in parallel
-// (the copy rate per CU grows with the number of issuing waves).
-// STAGES LDS stages of the BM x BKV A tile and SBS (default: STAGES) of the
-// BN x BKV B tile; OCC workgroups per CU.  With one more A stage than B
-// stages, A's copies run one K step further ahead (the streamed activation
-// operand arrives from HBM/MALL while the weight operand hits L2).
+// 32x32 MFMA tiles.  STAGES LDS stages of the BM x BKV and BN x BKV operand
+// tiles; OCC workgroups per CU.
 template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, bool AK, bool BKM, int EPI, bool SPLIT,
-          int BKV = 32, int SBS = 0>
+          int BKV = 32>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_kernel(const KArgs P) {
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int SA = STAGES, SB = SBS ? SBS : STAGES;
-  constexpr int LA = SA - 1, LB = SB - 1;  // copy lead of A and B, in K steps
-  static_assert(LB >= 1 && (LA == LB || LA == LB + 1), "A leads B by at most one step");
+  constexpr int S = STAGES;
+  static_assert(S >= 2, "the copies of a stage run while another is multiplied");
   constexpr int A_BYTES = BM * BKV * 2, B_BYTES = BN * BKV * 2;
   constexpr int A_BLK = A_BYTES / 1024, B_BLK = B_BYTES / 1024;
   // direct-to-LDS instructions per wave per K step (same count on every wave)
-  constexpr int LOADS_A = (A_BLK + NW - 1) / NW, LOADS_B = (B_BLK + NW - 1) / NW;
+  constexpr int LOADS_A = A_BLK / NW, LOADS_B = B_BLK / NW, NPIECE = LOADS_A + LOADS_B;
   static_assert(A_BLK % NW == 0 && B_BLK % NW == 0, "copies must split evenly over the waves");
+  static_assert((S - 2) * NPIECE <= 63, "vmcnt field");
   constexpr int KS = BKV / 16;
-  __shared__ __attribute__((aligned(1024))) char smem[SA * A_BYTES + SB * B_BYTES];
+  static_assert(KS % 2 == 0, "the fragment buffers alternate by sub-step");
+  __shared__ __attribute__((aligned(1024))) char smem[S * (A_BYTES + B_BYTES)];
 
   // ---- tile mapping.  The grid is one dimension of (batch or split) x
   // tiles, padded to a multiple of 8.  Workgroups are dealt round-robin over
@@ -415,7 +439,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_kernel(const KA
   if (P.causal == CAUSAL_A_LOWER) ke = min(ke, m0 + BM);
   if (P.causal == CAUSAL_A_UPPER) kb = max(kb, m0);
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
 
   f32x16 acc[TM][TN];
@@ -447,120 +471,149 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_kernel(const KA
 
   const int nk = (int)((ke - kb + BKV - 1) / BKV);
   const int krem = (int)((ke - kb) - (int64_t)(nk - 1) * BKV);  // valid k in the last step
-  char* const smem_b = smem + SA * A_BYTES;
-  // Copies of (virtual) step v: A tile v + LA and B tile v + LB, LOADS_A +
-  // LOADS_B one-block pieces per wave.  When A leads, B's pieces come first
-  // so that the wait for B(kt) leaves A(kt+1) in flight; when they lead
-  // equally, A's first (A(kt) older than B(kt)).
-  constexpr int NPIECE = LOADS_A + LOADS_B;
-  // With two or fewer stages of lead the copies are issued as early as
-  // possible (right after the first fragment reads); with three or more they
-  // are spread over the sub-steps (measured: each choice is 5-10 % faster
-  // where it is used).
-  constexpr bool SPREAD = LA >= 3;
-  auto issue_piece = [&](int v, int p) {
-    const bool is_b = LA > LB ? p < LOADS_B : p >= LOADS_A;
-    if (is_b) {
-      const int t = v + LB;
-      if (t >= 0 && t < nk)
-        issue_block<BN, BKM, BKV, NW>(Bb, P.ldb, n0, kb + (int64_t)t * BKV, P.N, ke, smem_b + (t % SB) * B_BYTES,
-                                      wave, lane, LA > LB ? p : p - LOADS_A);
+  const int n_full = krem < BKV ? nk - 1 : nk;                   // steps whose copies need no clamped k
+  char* const smem_b = smem + S * A_BYTES;
+  const char* src_a[LOADS_A];
+  const char* src_b[LOADS_B];
+#pragma unroll
+  for (int i = 0; i < LOADS_A; ++i) src_a[i] = block_src<BM, AK, BKV, NW>(Ab, P.lda, m0, kb, P.M, wave, lane, i);
+#pragma unroll
+  for (int i = 0; i < LOADS_B; ++i) src_b[i] = block_src<BN, BKM, BKV, NW>(Bb, P.ldb, n0, kb, P.N, wave, lane, i);
+  const int64_t adv_a = AK ? 2 * BKV : 2 * BKV * P.lda, adv_b = BKM ? 2 * BKV : 2 * BKV * P.ldb;
+  // copy p of the next whole K step into ring slot `slot`
+  auto issue = [&](int slot, int p) {
+    if (p < LOADS_A) {
+      copy_block<0>(src_a[p], smem + slot * A_BYTES + (wave * LOADS_A + p) * 1024);
+      src_a[p] += adv_a;
     } else {
-      const int t = v + LA;
-      if (t >= 0 && t < nk)
-        issue_block<BM, AK, BKV, NW>(Ab, P.lda, m0, kb + (int64_t)t * BKV, P.M, ke, smem + (t % SA) * A_BYTES,
-                                     wave, lane, LA > LB ? p - LOADS_B : p);
+      const int q = p - LOADS_A;
+      copy_block<0>(src_b[q], smem_b + slot * B_BYTES + (wave * LOADS_B + q) * 1024);
+      src_b[q] += adv_b;
     }
   };
+  // all copies of K step t, which may be the partial last one or past the end
+  auto issue_step = [&](int t, int slot) {
+    if (t < n_full) {
 #pragma unroll
-  for (int v = -LA; v < 0; ++v)
+      for (int p = 0; p < NPIECE; ++p) issue(slot, p);
+    } else if (t < nk) {
 #pragma unroll
-    for (int p = 0; p < NPIECE; ++p) issue_piece(v, p);
-
-  for (int kt = 0; kt < nk; ++kt) {
-    // A(kt) and B(kt) have landed once at most the loads issued after B(kt)
-    // are outstanding (loads complete in order): with d = the K steps left
-    // after this one (capped at LA), those are, for A leading, A(kt+1) and
-    // the copies of the LB-1 later steps, for equal leads the copies of the
-    // LB-1 later steps.  The barrier publishes every wave's copies and frees
-    // the stages read in the previous step (every wave has waited for its
-    // reads of them before its last MFMAs).
-    const int left = min(LA, nk - 1 - kt);
-    static_for<0, LA + 1>([&](auto D) {
-      constexpr int d = decltype(D)::value;
-      constexpr int y = [] {
-        int n = 0;
-        if (LA > LB) {
-          n += d >= 1 ? LOADS_A : 0;
-          for (int j = 1; j <= LB - 1; ++j) n += (j <= d ? LOADS_B : 0) + (j + 1 <= d ? LOADS_A : 0);
-        } else {
-          for (int j = 1; j <= LB - 1; ++j) n += j <= d ? LOADS_A + LOADS_B : 0;
-        }
-        return n;
-      }();
-      static_assert(y <= 63, "vmcnt field");
-      if (left == d) WAIT_VMCNT(y);
-    });
-    barrier_only();
-    char* sta = smem + (kt % SA) * A_BYTES;
-    char* stb = smem_b + (kt % SB) * B_BYTES;
-    if (kt == nk - 1 && krem < BKV) {
-      zero_tail<BM, AK, BKV>(sta, krem);
-      zero_tail<BN, BKM, BKV>(stb, krem);
-      __syncthreads();
+      for (int p = 0; p < LOADS_A; ++p)
+        issue_block<BM, AK, BKV, NW>(Ab, P.lda, m0, kb + (int64_t)t * BKV, P.M, ke, smem + slot * A_BYTES, wave,
+                                     lane, p);
+#pragma unroll
+      for (int p = 0; p < LOADS_B; ++p)
+        issue_block<BN, BKM, BKV, NW>(Bb, P.ldb, n0, kb + (int64_t)t * BKV, P.N, ke, smem_b + slot * B_BYTES, wave,
+                                      lane, p);
     }
-    const uint32_t sa = lds0 + (uint32_t)((kt % SA) * A_BYTES);
-    const uint32_t sbb = lds0 + (uint32_t)(SA * A_BYTES + (kt % SB) * B_BYTES);
-    // the first PF sub-steps' fragments are requested before anything else
-    // (the copies' address arithmetic then hides the LDS latency);
-    // afterwards the fragments of sub-step ks+PF are read while the MFMAs of
-    // ks run.  LDS reads return in order, so waiting until at most the reads
-    // of the younger sub-steps are outstanding suffices.
-    constexpr int PF = 1;  // sub-steps of fragments in flight (2 measured slower)
-    constexpr int NBUF = PF + 1;
-    u32x4 af[NBUF][TM], bfr[NBUF][TN];
-    static_for<0, PF>([&](auto KSI) {
+  };
+  // Fragments of sub-step ks live in buffer ks % 2.  K step kt begins with
+  // the last sub-step of step kt - 1 still to be multiplied (zeros before the
+  // first): its fragments are in registers, so the one barrier of a step
+  // both publishes the copies of step kt and frees the stage of step kt - 1,
+  // and the MFMAs of that sub-step cover the latency of the new stage's first
+  // fragment reads and carry the copies of step kt + S - 1 between them.
+  // (Reading a stage's first fragments behind the barrier and the copies
+  // behind those cost 2 x 0.15 us of each ~1.5 us step of a 256 x 256 x 64
+  // tile.)  The scheduling fences keep a cluster's MFMAs ahead of the next
+  // wait: the compiler otherwise sinks them below it, and they then wait for
+  // fragments they do not need.  What bounds the loop now is the rate of the
+  // operand copies per CU (45-75 GB/s whatever the number of stages and of
+  // active CUs; L2 prefetching raised it and moved nothing) and how little
+  // of it the MFMAs hide: 8192 x 8192 x 8192 takes 880 us (before: 1001),
+  // its copies alone 733, its reads and MFMAs alone 565.
+  u32x4 af[2][TM], bfr[2][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) af[1][i] = u32x4{0, 0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < TN; ++j) bfr[1][j] = u32x4{0, 0, 0, 0};
+  auto read_sub = [&](auto KSI, int slot) {
+    constexpr int ks = decltype(KSI)::value;
+    read_frags<BM, AK, BKV, TM, ks>(lds0 + (uint32_t)(slot * A_BYTES), a_off, af[ks & 1]);
+    read_frags<BN, BKM, BKV, TN, ks>(lds0 + (uint32_t)(S * A_BYTES + slot * B_BYTES), b_off, bfr[ks & 1]);
+  };
+  auto landed = [&](auto CB) {  // the buffer's reads have been waited for
+    constexpr int cb = decltype(CB)::value;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) after_wait(af[cb][i]);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) after_wait(bfr[cb][j]);
+  };
+  // the MFMAs (and row sums) of one buffer; COPY: with the copies of a whole
+  // K step into slot `slot` spread between them
+  auto multiply = [&](auto CB, auto COPY, int slot) {
+    constexpr int cb = decltype(CB)::value;
+    constexpr bool copy = decltype(COPY)::value != 0;
+    constexpr int PER = (NPIECE + TM * TN - 1) / (TM * TN);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[cb][i]),
+                                                            __builtin_bit_cast(bf16x8, bfr[cb][j]),
+                                                            acc[i][j], 0, 0, 0);
+        if constexpr (copy) {
+#pragma unroll
+          for (int p = (i * TN + j) * PER; p < (i * TN + j + 1) * PER; ++p)
+            if (p < NPIECE) issue(slot, p);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    if constexpr (!AK) {
+      if (rs_on) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) rsum[i] += sum_bf16x8(af[cb][i]);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // MAIN: step kt + S - 1 is a whole one (no branch inside)
+  auto k_step = [&](auto MAIN, int kt, int slot) {
+    constexpr bool main = decltype(MAIN)::value != 0;
+    const int pslot = slot == 0 ? S - 1 : slot - 1;  // of steps kt - 1 and kt + S - 1
+    if constexpr (main) {
+      WAIT_VMCNT((S - 2) * NPIECE);  // loads complete in order: step kt has landed
+      barrier_only();
+    } else {
+      const int left = min(S - 2, nk - 1 - kt);  // younger steps still in flight
+      static_for<0, S - 1>([&](auto D) {
+        constexpr int d = decltype(D)::value;
+        if (left == d) WAIT_VMCNT(d * NPIECE);
+      });
+      barrier_only();
+      if (kt == nk - 1 && krem < BKV) {
+        zero_tail<BM, AK, BKV>(smem + slot * A_BYTES, krem);
+        zero_tail<BN, BKM, BKV>(smem_b + slot * B_BYTES, krem);
+        __syncthreads();
+      }
+    }
+    read_sub(IntC<0>{}, slot);
+    if constexpr (!main) issue_step(kt + S - 1, pslot);
+    multiply(IntC<1>{}, IntC<main ? 1 : 0>{}, pslot);
+    static_for<0, KS - 1>([&](auto KSI) {
       constexpr int ks = decltype(KSI)::value;
-      read_frags<BM, AK, BKV, TM, ks>(sa, a_off, af[ks]);
-      read_frags<BN, BKM, BKV, TN, ks>(sbb, b_off, bfr[ks]);
+      read_sub(IntC<ks + 1>{}, slot);
+      lgkm_wait<NREAD>();
+      landed(IntC<ks & 1>{});
+      multiply(IntC<ks & 1>{}, IntC<0>{}, 0);
     });
-    if constexpr (!SPREAD) {
-#pragma unroll
-      for (int p = 0; p < NPIECE; ++p) issue_piece(kt, p);
-    }
-    static_for<0, KS>([&](auto KSI) {
-      constexpr int ks = decltype(KSI)::value, cb = ks % NBUF;
-      if constexpr (ks + PF < KS) {
-        read_frags<BM, AK, BKV, TM, ks + PF>(sa, a_off, af[(ks + PF) % NBUF]);
-        read_frags<BN, BKM, BKV, TN, ks + PF>(sbb, b_off, bfr[(ks + PF) % NBUF]);
-      }
-      constexpr int younger = (KS - 1 - ks < PF ? KS - 1 - ks : PF);
-      lgkm_wait<NREAD * younger>();
-#pragma unroll
-      for (int i = 0; i < TM; ++i) after_wait(af[cb][i]);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) after_wait(bfr[cb][j]);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[cb][i]),
-                                                              __builtin_bit_cast(bf16x8, bfr[cb][j]),
-                                                              acc[i][j], 0, 0, 0);
-      if constexpr (!AK) {
-        if (rs_on) {
-#pragma unroll
-          for (int i = 0; i < TM; ++i) rsum[i] += sum_bf16x8(af[cb][i]);
-        }
-      }
-      // deep pipelines: this sub-step's share of the next stage's copies,
-      // whose address arithmetic runs while the MFMAs just issued execute
-      if constexpr (SPREAD) {
-#pragma unroll
-        for (int p = ks * NPIECE / KS; p < (ks + 1) * NPIECE / KS; ++p) issue_piece(kt, p);
-      }
-    });
+    // the last sub-step's fragments are complete before the back edge (no
+    // register of a read in flight crosses it) and before the next barrier
+    lgkm_wait<0>();
+    landed(IntC<1>{});
+  };
+  for (int t = 0; t < S - 1; ++t) issue_step(t, t);
+  int kt = 0, slot = 0;
+  for (; kt + S - 1 < n_full; ++kt) {
+    k_step(IntC<1>{}, kt, slot);
+    slot = slot + 1 == S ? 0 : slot + 1;
   }
+  for (; kt < nk; ++kt) {
+    k_step(IntC<0>{}, kt, slot);
+    slot = slot + 1 == S ? 0 : slot + 1;
+  }
+  multiply(IntC<1>{}, IntC<0>{}, 0);
 
   // ---- epilogue.  32x32 accumulator layout: lane l, register r holds
   // row (r/4)*8 + (l/32)*4 + r%4, column l%32 of the 32x32 block.  Each block
@@ -586,7 +639,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_kernel(const KA
     }
   }
   constexpr int LDW = 40;  // floats per staged row: rows r and r + 4 sit 32 banks apart
-  static_assert(NW * 32 * LDW * 4 <= SA * A_BYTES + SB * B_BYTES, "staging fits in the stages");
+  static_assert(NW * 32 * LDW * 4 <= S * (A_BYTES + B_BYTES), "staging fits in the stages");
   __syncthreads();  // every wave has finished reading the stages
   float* const stg = reinterpret_cast<float*>(smem) + wave * 32 * LDW;
   const int64_t c_off = zo * P.c_outer + zi * P.c_inner;
@@ -716,8 +769,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const KArgs P) {
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int STG, int OCC, bool AK, bool BKM, int EPI, int BKV = 32,
-          int SBS = 0>
+template <int BM, int BN, int WGM, int WGN, int STG, int OCC, bool AK, bool BKM, int EPI, int BKV = 32>
 hipError_t launch_tiles(const KArgs& P, int batch, hipStream_t s) {
   const int64_t n_log = (int64_t)P.tiles_m * P.tiles_n * (P.splits > 1 ? P.splits : batch);
   if (n_log >= (1ll << 31) - 8) return hipErrorInvalidValue;
@@ -725,7 +777,7 @@ hipError_t launch_tiles(const KArgs& P, int batch, hipStream_t s) {
   constexpr int NT = 64 * WGM * WGN;
   if constexpr (EPI == EPI_F32 || EPI == EPI_UPDATE) {
     if (P.splits > 1) {
-      gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, true, BKV, SBS><<<grid, NT, 0, s>>>(P);
+      gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, true, BKV><<<grid, NT, 0, s>>>(P);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
       const int64_t groups = P.M * cdiv(P.N, 4);
@@ -734,7 +786,7 @@ hipError_t launch_tiles(const KArgs& P, int batch, hipStream_t s) {
       return hipGetLastError();
     }
   }
-  gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, false, BKV, SBS><<<grid, NT, 0, s>>>(P);
+  gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, false, BKV><<<grid, NT, 0, s>>>(P);
   return hipGetLastError();
 }
 
@@ -833,12 +885,12 @@ std::string gemm_check(const Gemm& g, bool f32_operands) {
 // and K-step length.
 struct TileShape { int bm, bn; };
 static const TileShape kShapes[] = {
-    {256, 256},  // 0: 4x2 waves (each 64x128), 2 stages of K 64, 1/CU  (8 waves/CU)
+    {256, 256},  // 0: 2x4 waves (each 128x64), 2 stages of K 64, 1/CU  (8 waves/CU)
     {128, 128},  // 1: 2x4 waves (each 64x32),  3 stages of K 32, 3/CU  (24 waves/CU)
     {128, 64},   // 2: 2x2 waves (each 64x32),  4 stages of K 32, 3/CU  (12 waves/CU)
     {128, 128},  // 3: 2x4 waves (each 64x32),  2 stages of K 64, 2/CU  (16 waves/CU)
-    {256, 256},  // 4: 4x2 waves (each 64x128), 4 stages of K 32, 1/CU  (8 waves/CU)
-    {256, 128},  // 5: 4x2 waves (each 64x64),  3 stages of K 32, 1/CU  (8 waves/CU)
+    {256, 256},  // 4: 2x4 waves (each 128x64), 4 stages of K 32, 1/CU  (8 waves/CU)
+    {256, 128},  // 5: 4x2 waves (each 64x64),  3 stages of K 64, 1/CU  (8 waves/CU)
 };
 constexpr int kNumCfg = 6;
 
@@ -859,11 +911,11 @@ hipError_t launch_gemm_bf16_cfg(const Gemm& g, int cfg, int splits, hipStream_t 
     }
   }
   switch (cfg) {
-    case 0: return dispatch_epi<256, 256, 4, 2, 2, 1, 64>(g, P, s);
+    case 0: return dispatch_epi<256, 256, 2, 4, 2, 1, 64>(g, P, s);
     case 1: return dispatch_epi<128, 128, 2, 4, 3, 3, 32>(g, P, s);
     case 2: return dispatch_epi<128, 64, 2, 2, 4, 3, 32>(g, P, s);
-    case 4: return dispatch_epi<256, 256, 4, 2, 4, 1, 32>(g, P, s);
-    case 5: return dispatch_epi<256, 128, 4, 2, 3, 1, 32>(g, P, s);
+    case 4: return dispatch_epi<256, 256, 2, 4, 4, 1, 32>(g, P, s);
+    case 5: return dispatch_epi<256, 128, 4, 2, 3, 1, 64>(g, P, s);
     default: return dispatch_epi<128, 128, 2, 4, 2, 2, 64>(g, P, s);
   }
 }
@@ -883,7 +935,7 @@ hipError_t launch_gemm_bf16_cfg(const Gemm& g, int cfg, int splits, hipStream_t 
 //    64, two workgroups per CU; for m-major B, split-K fills the 512
 //    workgroup slots of one round (largest split with tiles x split <= 512);
 //  - dW with at least 512 tiles of 128x128 otherwise: 256x128, three stages
-//    of K 32;
+//    of K 64;
 //  - otherwise (forward products with bf16/GELU epilogues): 128x128 with K
 //    steps of 32 and three stages (more loads in flight for short K).
 // Split-K (float32 partials, fixed-order sum) only with K >= 1536, at least
