@@ -385,10 +385,10 @@ __device__ __forceinline__ void barrier_only() {
 
 // WGM x WGN waves per workgroup; each wave owns a (BM/WGM) x (BN/WGN) block of
 // 32x32 MFMA tiles.  STAGES LDS stages of the BM x BKV and BN x BKV operand
-// tiles; OCC workgroups per CU.
-template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, bool AK, bool BKM, int EPI, bool SPLIT,
-          int BKV = 32>
-__global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_kernel(const KArgs P) {
+// tiles.  This is the work of one workgroup: item `lid` of P's flat list of
+// (batch or split, tile) work items.
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool AK, bool BKM, int EPI, bool SPLIT, int BKV>
+__device__ __forceinline__ void gemm_item(const KArgs& P, int lid) {
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -404,17 +404,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_kernel(const KA
   static_assert(KS % 2 == 0, "the fragment buffers alternate by sub-step");
   __shared__ __attribute__((aligned(1024))) char smem[S * (A_BYTES + B_BYTES)];
 
-  // ---- tile mapping.  The grid is one dimension of (batch or split) x
-  // tiles, padded to a multiple of 8.  Workgroups are dealt round-robin over
-  // the 8 XCDs (each with its own L2), so hardware id h runs on XCD h % 8:
-  // the remap gives every XCD a contiguous range of logical ids, i.e. whole
-  // bands of tiles of one batch/split that share operand rows.  Inside a
-  // batch/split, tiles go in groups of 8 tile-rows for L2 reuse of B.
+  // tiles go in groups of 8 tile-rows for L2 reuse of B
   const int n_tiles = P.tiles_m * P.tiles_n;
-  const int n_log = n_tiles * (SPLIT ? P.splits : P.nz);
-  const int h = blockIdx.x;
-  const int lid = (h & 7) * (int)(gridDim.x >> 3) + (h >> 3);
-  if (lid >= n_log) return;
   const int zz = lid / n_tiles, id = lid % n_tiles;
   constexpr int GROUP = 8;
   const int width = GROUP * P.tiles_n;
@@ -678,6 +669,43 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_kernel(const KA
   }
 }
 
+// The logical work item of a hardware workgroup.  The grid is one dimension
+// of work items, padded to a multiple of 8.  Workgroups are dealt round-robin
+// over the 8 XCDs (each with its own L2), so hardware id h runs on XCD h % 8:
+// the remap gives every XCD a contiguous range of logical ids, i.e. whole
+// bands of tiles of one batch/split that share operand rows.
+__device__ __forceinline__ int work_item() {
+  const int h = blockIdx.x;
+  return (h & 7) * (int)(gridDim.x >> 3) + (h >> 3);
+}
+
+// OCC: workgroups per CU.
+template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, bool AK, bool BKM, int EPI, bool SPLIT, int BKV>
+__global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_kernel(const KArgs P) {
+  const int lid = work_item();
+  if (lid >= P.tiles_m * P.tiles_n * (SPLIT ? P.splits : P.nz)) return;
+  gemm_item<BM, BN, WGM, WGN, STAGES, AK, BKM, EPI, SPLIT, BKV>(P, lid);
+}
+
+// Several products dW = dY^T X in one launch (GemmGroup): the work items of
+// all of them numbered one product after the other.
+constexpr int MAX_GROUP = GEMM_GROUP_MAX;
+struct GroupArgs {
+  int32_t n;
+  int32_t first[MAX_GROUP + 1];   // first work item of each product
+  int32_t rfirst[MAX_GROUP + 1];  // first workgroup of each product's split-K sum
+  KArgs p[MAX_GROUP];
+};
+
+template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool SPLIT, int BKV>
+__global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_group_kernel(const GroupArgs G) {
+  const int lid = work_item();
+  if (lid >= G.first[G.n]) return;
+  int i = 0;
+  while (i + 1 < G.n && lid >= G.first[i + 1]) ++i;
+  gemm_item<BM, BN, WGM, WGN, STAGES, false, false, EPI, SPLIT, BKV>(G.p[i], lid - G.first[i]);
+}
+
 // Sum over the splits, in split order, of the partials of four consecutive
 // columns (ne of them valid; one 128-bit load per split when vec).  The
 // loads of up to eight splits are issued before the first add, so a thread
@@ -713,10 +741,9 @@ __device__ __forceinline__ f32x4 sum_partials4(const float* src, int64_t total, 
 // accesses when N and ldc are multiples of 4 and every pointer is 16-byte
 // aligned.  The thread of a row's first group also sums the row-sum partials.
 template <int EPI>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const KArgs P) {
+__device__ __forceinline__ void splitk_reduce_item(const KArgs& P, int64_t idx) {
   static_assert(EPI == EPI_F32 || EPI == EPI_UPDATE, "split-K only with the float32 or update epilogue");
   const int64_t nq = (P.N + 3) / 4;
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= P.M * nq) return;
   const int64_t m = idx / nq;
   const int64_t n = (idx - m * nq) * 4;
@@ -769,7 +796,20 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const KArgs P) {
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int STG, int OCC, bool AK, bool BKM, int EPI, int BKV = 32>
+template <int EPI>
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const KArgs P) {
+  splitk_reduce_item<EPI>(P, (int64_t)blockIdx.x * 256 + threadIdx.x);
+}
+
+template <int EPI>
+__global__ __launch_bounds__(256) void splitk_reduce_group_kernel(const GroupArgs G) {
+  const int b = blockIdx.x;
+  int i = 0;
+  while (i + 1 < G.n && b >= G.rfirst[i + 1]) ++i;
+  splitk_reduce_item<EPI>(G.p[i], (int64_t)(b - G.rfirst[i]) * 256 + threadIdx.x);
+}
+
+template <int BM, int BN, int WGM, int WGN, int STG, int OCC, bool AK, bool BKM, int EPI, int BKV>
 hipError_t launch_tiles(const KArgs& P, int batch, hipStream_t s) {
   const int64_t n_log = (int64_t)P.tiles_m * P.tiles_n * (P.splits > 1 ? P.splits : batch);
   if (n_log >= (1ll << 31) - 8) return hipErrorInvalidValue;
@@ -878,27 +918,109 @@ std::string gemm_check(const Gemm& g, bool f32_operands) {
   return "";
 }
 
-// Tile configurations: tile, wave grid, LDS stages, workgroups per CU, K
-// step.  The copy rate into LDS grows with the number of waves issuing
-// direct-to-LDS loads, and each K step costs one wait and one barrier, so
-// the configurations trade tile size (operand reuse) against waves per CU
-// and K-step length.
-struct TileShape { int bm, bn; };
-static const TileShape kShapes[] = {
-    {256, 256},  // 0: 2x4 waves (each 128x64), 2 stages of K 64, 1/CU  (8 waves/CU)
-    {128, 128},  // 1: 2x4 waves (each 64x32),  3 stages of K 32, 3/CU  (24 waves/CU)
-    {128, 64},   // 2: 2x2 waves (each 64x32),  4 stages of K 32, 3/CU  (12 waves/CU)
-    {128, 128},  // 3: 2x4 waves (each 64x32),  2 stages of K 64, 2/CU  (16 waves/CU)
-    {256, 256},  // 4: 2x4 waves (each 128x64), 4 stages of K 32, 1/CU  (8 waves/CU)
-    {256, 128},  // 5: 4x2 waves (each 64x64),  3 stages of K 64, 1/CU  (8 waves/CU)
+// Tile configurations.  Larger tiles read fewer operand bytes per FLOP,
+// smaller ones fill the chip and overlap one workgroup's epilogue with
+// another's products.  step: us per 64 k of a workgroup, alone on a quarter
+// of the CUs or fewer (lo) and with every CU's slots full (hi); fix: us
+// besides (first copies, epilogue arithmetic, launch).  Measured on the
+// linear layers of the GPT-2-small, GPT-2-medium and 1.3B stacks with random
+// operands from HBM.
+struct TileCfg {
+  int bm, bn, occ;
+  float step_lo, step_hi, fix;
 };
-constexpr int kNumCfg = 6;
+enum TileId { T256x256 = 0, T256x192, T256x128, T128x192, T128x128, T128x64, T64x64, kNumCfg };
+static const TileCfg kCfgs[kNumCfg] = {
+    {256, 256, 1, 1.30f, 1.75f, 3.0f},  // 2x4 waves (each 128x64), 2 stages of K 64
+    {256, 192, 1, 1.25f, 1.55f, 3.0f},  // 4x2 waves (each 64x96),  2 stages of K 64
+    {256, 128, 1, 0.85f, 1.10f, 3.0f},  // 4x2 waves (each 64x64),  3 stages of K 64
+    {128, 192, 1, 0.70f, 0.90f, 3.0f},  // 4x2 waves (each 32x96),  3 stages of K 64
+    {128, 128, 2, 0.70f, 1.15f, 3.0f},  // 2x4 waves (each 64x32),  2 stages of K 64
+    {128, 64, 3, 0.41f, 1.10f, 2.5f},   // 2x2 waves (each 64x32),  4 stages of K 32
+    {64, 64, 4, 0.38f, 0.72f, 2.0f},    // 2x2 waves (each 32x32),  2 stages of K 64
+};
+
+namespace {
+template <int BM, int BN, int WGM, int WGN, int STG, int OCC, int BKV, int EPI>
+hipError_t launch_group_epi(const GroupArgs& G, bool split, hipStream_t s) {
+  const dim3 grid((unsigned)((G.first[G.n] + 7) / 8 * 8));
+  constexpr int NT = 64 * WGM * WGN;
+  if (!split) {
+    gemm_bf16_group_kernel<BM, BN, WGM, WGN, STG, OCC, EPI, false, BKV><<<grid, NT, 0, s>>>(G);
+    return hipGetLastError();
+  }
+  gemm_bf16_group_kernel<BM, BN, WGM, WGN, STG, OCC, EPI, true, BKV><<<grid, NT, 0, s>>>(G);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  splitk_reduce_group_kernel<EPI><<<(unsigned)G.rfirst[G.n], 256, 0, s>>>(G);
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int WGM, int WGN, int STG, int OCC, int BKV>
+hipError_t launch_group(const GroupArgs& G, int epi, bool split, hipStream_t s) {
+  return epi == EPI_UPDATE ? launch_group_epi<BM, BN, WGM, WGN, STG, OCC, BKV, EPI_UPDATE>(G, split, s)
+                           : launch_group_epi<BM, BN, WGM, WGN, STG, OCC, BKV, EPI_F32>(G, split, s);
+}
+}  // namespace
+
+// The products share K, the epilogue (float32 or the weight update) and the
+// split-K workspace, which splits > 1 needs room in for all of them.
+hipError_t launch_gemm_bf16_group_cfg(const Gemm* g, int n, int cfg, int splits, hipStream_t s) {
+  if (n < 1 || n > MAX_GROUP || cfg < 0 || cfg >= kNumCfg) return hipErrorInvalidValue;
+  GroupArgs G;
+  memset(&G, 0, sizeof(G));
+  G.n = n;
+  const int BM = kCfgs[cfg].bm, BN = kCfgs[cfg].bn;
+  const int64_t K = g[0].K;
+  size_t per_split = 0;
+  for (int i = 0; i < n; ++i) {
+    if (g[i].K != K || g[i].epi != g[0].epi || g[i].a_kmajor || g[i].b_kmajor || g[i].batch != 1 || g[i].M < 1 ||
+        g[i].N < 1 || (g[i].epi != EPI_F32 && g[i].epi != EPI_UPDATE))
+      return hipErrorInvalidValue;
+    per_split += ((size_t)g[i].M * g[i].N + (g[i].rowsum ? g[i].M : 0)) * 4;
+    per_split = (per_split + 255) / 256 * 256;
+  }
+  if (!g[0].splitk_ws) splits = 1;
+  while (splits > 1 && splits * per_split > g[0].splitk_ws_bytes) --splits;
+  int64_t k_per = K;
+  if (splits > 1) {
+    k_per = cdiv(cdiv(K, splits), 32) * 32;
+    splits = (int)cdiv(K, k_per);
+  }
+  char* part = (char*)g[0].splitk_ws;
+  int64_t items = 0, rblocks = 0;
+  for (int i = 0; i < n; ++i) {
+    KArgs& P = G.p[i];
+    P = make_args(g[i]);
+    P.tiles_m = (int)cdiv(P.M, BM);
+    P.tiles_n = (int)cdiv(P.N, BN);
+    G.first[i] = (int)items;
+    G.rfirst[i] = (int)rblocks;
+    items += (int64_t)P.tiles_m * P.tiles_n * splits;
+    if (splits > 1) {
+      P.splits = splits;
+      P.k_per_split = k_per;
+      P.partial = (float*)part;
+      part += (((size_t)P.M * P.N + (P.rowsum ? P.M : 0)) * 4 * splits + 255) / 256 * 256;
+      rblocks += cdiv(P.M * cdiv(P.N, 4), 256);
+    }
+    if (items >= (1ll << 31) - 8 || rblocks >= (1ll << 31)) return hipErrorInvalidValue;
+  }
+  G.first[n] = (int)items;
+  G.rfirst[n] = (int)rblocks;
+  switch (cfg) {
+    case T256x256: return launch_group<256, 256, 2, 4, 2, 1, 64>(G, g[0].epi, splits > 1, s);
+    case T256x128: return launch_group<256, 128, 4, 2, 3, 1, 64>(G, g[0].epi, splits > 1, s);
+    case T128x128: return launch_group<128, 128, 2, 4, 2, 2, 64>(G, g[0].epi, splits > 1, s);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 hipError_t launch_gemm_bf16_cfg(const Gemm& g, int cfg, int splits, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return hipSuccess;
   if (cfg < 0 || cfg >= kNumCfg) return hipErrorInvalidValue;
   KArgs P = make_args(g);
-  const int BM = kShapes[cfg].bm, BN = kShapes[cfg].bn;
+  const int BM = kCfgs[cfg].bm, BN = kCfgs[cfg].bn;
   P.tiles_m = (int)cdiv(g.M, BM);
   P.tiles_n = (int)cdiv(g.N, BN);
   if (splits > 1 && g.batch == 1 && g.splitk_ws && (g.epi == EPI_F32 || g.epi == EPI_UPDATE) && g.M <= 65535) {
@@ -911,61 +1033,86 @@ hipError_t launch_gemm_bf16_cfg(const Gemm& g, int cfg, int splits, hipStream_t 
     }
   }
   switch (cfg) {
-    case 0: return dispatch_epi<256, 256, 2, 4, 2, 1, 64>(g, P, s);
-    case 1: return dispatch_epi<128, 128, 2, 4, 3, 3, 32>(g, P, s);
-    case 2: return dispatch_epi<128, 64, 2, 2, 4, 3, 32>(g, P, s);
-    case 4: return dispatch_epi<256, 256, 2, 4, 4, 1, 32>(g, P, s);
-    case 5: return dispatch_epi<256, 128, 4, 2, 3, 1, 64>(g, P, s);
-    default: return dispatch_epi<128, 128, 2, 4, 2, 2, 64>(g, P, s);
+    case T256x256: return dispatch_epi<256, 256, 2, 4, 2, 1, 64>(g, P, s);
+    case T256x192: return dispatch_epi<256, 192, 4, 2, 2, 1, 64>(g, P, s);
+    case T256x128: return dispatch_epi<256, 128, 4, 2, 3, 1, 64>(g, P, s);
+    case T128x192: return dispatch_epi<128, 192, 4, 2, 3, 1, 64>(g, P, s);
+    case T128x128: return dispatch_epi<128, 128, 2, 4, 2, 2, 64>(g, P, s);
+    case T128x64: return dispatch_epi<128, 64, 2, 2, 4, 3, 32>(g, P, s);
+    default: return dispatch_epi<64, 64, 2, 2, 2, 4, 64>(g, P, s);
   }
 }
 
-// Tile choice (measured on the GPT-2-small shapes with random operands
-// arriving from HBM, as inside the step -- under the power limit the clock,
-// and so the ranking, depends on the data):
-//  - N <= 64 (attention head width): 128x64;
-//  - both output dimensions >= 2048, K >= 4096 and at least 256 tiles:
-//    256x256 with K steps of 64;
-//  - float32 output and K >= 16384 (the tied head's dX over the vocabulary):
-//    256x256 with four stages of K 32 and an 8-way split of K;
-//  - dW = dY^T X with at least 256 tiles of 256x256 (the head's dW): 256x256
-//    with K steps of 64;
-//  - float32 outputs with an m-major B (dX = dY W, and dW = dY^T X with fewer
-//    than 512 tiles) and float32 forward products: 128x128 with K steps of
-//    64, two workgroups per CU; for m-major B, split-K fills the 512
-//    workgroup slots of one round (largest split with tiles x split <= 512);
-//  - dW with at least 512 tiles of 128x128 otherwise: 256x128, three stages
-//    of K 64;
-//  - otherwise (forward products with bf16/GELU epilogues): 128x128 with K
-//    steps of 32 and three stages (more loads in flight for short K).
-// Split-K (float32 partials, fixed-order sum) only with K >= 1536, at least
-// 512 K per split, at most 8 splits.
+// Estimated time (us) of `items` work items of `steps` K steps of 64 each on
+// one tile configuration, with `bytes` of epilogue traffic per output
+// element: whole rounds of the chip's slots, then a last round whose steps
+// and epilogue are faster the emptier it is.
+static float est_items(const TileCfg& t, int64_t items, float steps, float bytes) {
+  const int64_t slots = 256 * (int64_t)t.occ;
+  // 25 KB/us of epilogue traffic per CU with all CUs writing (6.4 TB/s);
+  // workgroups that share a CU hide part of it behind the next round's products
+  const float epi = bytes * t.bm * t.bn * t.occ / 25e3f;
+  const float round = steps * t.step_hi + t.fix + epi * (t.occ > 1 ? 0.6f : 1.0f);
+  const int64_t full = items / slots, rest = items % slots;
+  float us = full * round;
+  if (rest > 0) {
+    // the last round takes as long as its fullest CU (one workgroup per CU:
+    // the operand stream slows with the share of CUs that are busy)
+    const float f = t.occ > 1 ? (float)(cdiv(rest, 256) - 1) / (float)(t.occ - 1) : (float)rest / slots;
+    us += steps * (t.step_lo + (t.step_hi - t.step_lo) * f) + t.fix + epi * (float)rest / slots;
+  }
+  return us;
+}
+
+// Tile and split of K for a product or a group of products with the same K:
+// the smallest estimate over the configurations and splits, the split's
+// partial sums written and read back at 4.5 TB/s by a second launch (8 us).
+// A split leaves at least 512 k each, at most 8 of them.
+struct Plan {
+  int cfg = T128x128, splits = 1;
+};
+static Plan choose(const Gemm* g, int n, bool group) {
+  const bool splittable = g[0].batch == 1 && (g[0].epi == EPI_F32 || g[0].epi == EPI_UPDATE) && g[0].splitk_ws;
+  double outputs = 0.0;
+  size_t per_split = 0;
+  for (int i = 0; i < n; ++i) {
+    outputs += (double)g[i].M * g[i].N;
+    per_split += ((size_t)g[i].M * g[i].N + (g[i].rowsum ? g[i].M : 0)) * 4 + 256;
+  }
+  float bytes = g[0].epi == EPI_F32 ? 4.f : g[0].epi == EPI_BF16 ? 2.f : g[0].epi == EPI_UPDATE ? 30.f : 4.f;
+  if (g[0].epi == EPI_F32 && g[0].aux) bytes += 4.f;
+  const int64_t max_split = splittable ? std::min<int64_t>(8, g[0].K / 512) : 1;
+  Plan best;
+  float best_us = 3.4e38f;
+  for (int c = 0; c < kNumCfg; ++c) {
+    if (group && c != T256x256 && c != T256x128 && c != T128x128) continue;
+    const TileCfg& t = kCfgs[c];
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += cdiv(g[i].M, t.bm) * cdiv(g[i].N, t.bn) * g[i].batch;
+    for (int sp = 1; sp <= std::max<int64_t>(1, max_split); ++sp) {
+      if (sp > 1 && (sp * per_split > g[0].splitk_ws_bytes || g[0].M > 65535)) break;
+      // an m-major A (dW) is read with twice the LDS reads: steps take an eighth longer
+      const float steps = (float)cdiv(cdiv(g[0].K, sp), 64) * (g[0].a_kmajor ? 1.0f : 1.12f);
+      float us = est_items(t, tiles * sp, steps, sp > 1 ? 4.f : bytes);
+      if (sp > 1) us += 8.f + (float)(outputs * (4.0 * sp + bytes) / 4.5e6);
+      if (us < best_us) {
+        best_us = us;
+        best = Plan{c, sp};
+      }
+    }
+  }
+  return best;
+}
+
+hipError_t launch_gemm_bf16_group(const Gemm* g, int n, hipStream_t s) {
+  const Plan p = choose(g, n, true);
+  return launch_gemm_bf16_group_cfg(g, n, p.cfg, p.splits, s);
+}
+
 hipError_t launch_gemm_bf16(const Gemm& g, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return hipSuccess;
-  auto tiles = [&](int bm, int bn) { return cdiv(g.M, bm) * cdiv(g.N, bn) * g.batch; };
-  const bool f32_out = g.epi == EPI_F32 || g.epi == EPI_UPDATE;
-  const bool splittable = g.batch == 1 && g.K >= 1536 && f32_out;
-  const int64_t max_split = std::min<int64_t>(8, g.K / 512);
-  auto split_for = [&](int64_t t, int64_t want) {
-    if (!splittable || t >= want) return 1;
-    return (int)std::min<int64_t>(std::max<int64_t>(2, cdiv(want, t)), max_split);
-  };
-  auto fill_split = [&](int64_t t, int64_t slots) {
-    if (!splittable) return 1;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(slots / t, max_split));
-  };
-  if (g.N <= 64) return launch_gemm_bf16_cfg(g, 2, 1, s);
-  // 256x256 tiles: long K with at least one round of tiles, or enough tiles
-  // (four rounds) for any K (the tied head's forward product)
-  if (g.M >= 2048 && g.N >= 2048 && tiles(256, 256) >= 256 && (g.K >= 4096 || tiles(256, 256) >= 1024))
-    return launch_gemm_bf16_cfg(g, 0, split_for(tiles(256, 256), 256), s);
-  if (splittable && g.K >= 16384 && g.a_kmajor) return launch_gemm_bf16_cfg(g, 4, (int)max_split, s);
-  if (f32_out && !g.a_kmajor && !g.b_kmajor && tiles(256, 256) >= 256) return launch_gemm_bf16_cfg(g, 0, 1, s);
-  const int64_t t = tiles(128, 128);
-  if (f32_out && !g.b_kmajor && (g.a_kmajor || t < 512)) return launch_gemm_bf16_cfg(g, 3, fill_split(t, 512), s);
-  if (f32_out && g.a_kmajor && g.b_kmajor) return launch_gemm_bf16_cfg(g, 3, 1, s);
-  if (f32_out && !g.a_kmajor && !g.b_kmajor) return launch_gemm_bf16_cfg(g, 5, 1, s);
-  return launch_gemm_bf16_cfg(g, 1, split_for(t, 512), s);
+  const Plan p = choose(&g, 1, false);
+  return launch_gemm_bf16_cfg(g, p.cfg, p.splits, s);
 }
 
 }  // namespace layup

@@ -167,9 +167,10 @@ enum Causal : int { CAUSAL_NONE = 0, CAUSAL_OUT_LOWER = 1, CAUSAL_A_LOWER = 2, C
 // Validates shapes/alignment; returns a message or empty string.
 std::string gemm_check(const Gemm& g, bool f32_operands);
 hipError_t launch_gemm_bf16(const Gemm& g, hipStream_t stream);
-// explicit tile configuration (0 = 256x256 K64, 1 = 128x128 K32, 2 = 128x64 K32, 3 = 128x128 K64,
-// 4 = 256x256 K32 four stages, 5 = 256x128 K64)
-hipError_t launch_gemm_bf16_cfg(const Gemm& g, int cfg, int splits, hipStream_t stream);
+// Up to four products dW = dY^T X of the same K and epilogue (float32 or the
+// weight update; batch 1) in one launch; the split-K workspace is g[0]'s.
+constexpr int GEMM_GROUP_MAX = 4;
+hipError_t launch_gemm_bf16_group(const Gemm* g, int n, hipStream_t stream);
 hipError_t launch_gemm_f32(const Gemm& g, hipStream_t stream);
 
 // ------------------------------------------------------------ glue kernels

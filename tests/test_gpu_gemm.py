@@ -271,3 +271,28 @@ def test_gemm_f32_tiles_and_remainders(ak, bk, M, N, K, ld):
     torch.cuda.synchronize()
     bound = 1.01 * (K + 1) * 2.0 ** -24 * (a.abs() @ b.abs())
     assert torch.all((C.cpu().double() - a @ b).abs() <= bound)
+
+
+@pytest.mark.parametrize("layout", ["kk", "kn", "mn"])
+@pytest.mark.parametrize("M,N", [(8192, 768), (8192, 3072), (4104, 4096), (2048, 8192), (1368, 3304), (520, 264), (72, 40)])
+@pytest.mark.parametrize("K", [8, 64, 72, 128, 200, 264])
+def test_gemm_tiles_and_short_k(layout, M, N, K):
+    """Every tile configuration (the choice goes by the sizes) at the edges of
+    its pipeline: fewer K steps than stages, exactly as many, one more, and
+    partial last steps.  Bound per element: a float32 sum of K exact products
+    in any order, 2 (K + 8) 2^-24 of the sum of absolute values (the factor
+    two covers adders that truncate)."""
+    ak, bk = {"kk": (True, True), "kn": (True, False), "mn": (False, False)}[layout]
+    g = torch.Generator(device=DEV).manual_seed(M + 3 * N + 5 * K)
+    A = torch.randn((M, K) if ak else (K, M), device=DEV, generator=g).to(torch.bfloat16)
+    B = torch.randn((N, K) if bk else (K, N), device=DEV, generator=g).to(torch.bfloat16)
+    C = torch.full((M, N), float("nan"), device=DEV)
+    rs = None if ak else torch.full((M,), float("nan"), device=DEV)
+    LU.layup_gemm_bf16(LU.gemm_desc(A, B, C, M, N, K, K if ak else M, K if bk else N, N, ak, bk, True, a_rowsum=rs),
+                       torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    a = (A if ak else A.t().contiguous()).double()
+    b = (B.t().contiguous() if bk else B).double()
+    assert torch.all((C.double() - a @ b).abs() <= 2 * (K + 8) * 2.0 ** -24 * (a.abs() @ b.abs()))
+    if rs is not None:
+        assert torch.all((rs.double() - a.sum(1)).abs() <= 2 * (K + 8) * 2.0 ** -24 * a.abs().sum(1))
