@@ -162,7 +162,7 @@ struct layup_ctx {
   // optional timing of the linear layers' backward GEMMs (events around each)
   bool gemm_timing = false;
   std::vector<hipEvent_t> gt_events;  // start/stop pairs
-  int gt_used = 0;
+  int gt_used = 0, gt_gemms = 0;      // events used, GEMMs they cover
   double gt_flops = 0.0;
   bool have_join = false;
   std::string err;
@@ -188,28 +188,29 @@ struct layup_ctx {
   float* dh = nullptr;
   float* da = nullptr;
   bf16_t* do16 = nullptr;
-  // The operands a linear layer's dW GEMM and bias sum read (dY), double-
-  // buffered by block parity: when the update stream differs from the
-  // compute stream, those dW GEMMs and sums run on the update stream,
-  // concurrently with the next layers' backward on the compute stream.
-  //   dyA: bf16 of the block's output gradient (MLP output projection)
+  // bf16 dY operands of a block's linear layers (read by both their dX and dW
+  // GEMMs), double-buffered by block parity: the dW GEMMs may run on the
+  // update stream while the next block's backward writes its own:
+  //   dyA: the block's output gradient (MLP output projection)
   //   dfb: GELU backward (MLP input projection)
-  //   dyB: bf16 of the gradient after the attention residual (attention proj)
+  //   dyB: the gradient after the attention residual (attention projection)
   //   dqb: dQ, dK, dV (qkv projection)
-  bf16_t *dyA[2] = {nullptr, nullptr}, *dfb[2] = {nullptr, nullptr};
-  bf16_t *dyB[2] = {nullptr, nullptr}, *dqb[2] = {nullptr, nullptr};
-  // ev_mid[p]: the first half of block parity p's operands written (dfb, dyB;
-  // compute stream) -- the others (dyA, dqb) are covered by the unit events;
-  // ev_rd[k][p]: operand k's dW GEMM and bias sum done (update stream);
-  hipEvent_t ev_mid[2] = {}, ev_rd[4][2] = {};
-  hipEvent_t ev_head = nullptr;  // the head's dW done (update stream)
+  bf16_t *dyA[2] = {}, *dfb[2] = {}, *dyB[2] = {}, *dqb[2] = {};
+  hipEvent_t ev_rd[2] = {};      // dW GEMMs of block parity q done (update stream)
   hipEvent_t ev_sort = nullptr;  // the token sort done (update stream)
-  hipEvent_t ev_fwd_half = nullptr;  // the forward's second half done (update stream)
-  bool unit_recorded = false;  // the backward recorded its unit event itself
   float* ln_part = nullptr;
   float *splitk = nullptr, *splitk_su = nullptr;
   size_t splitk_bytes = 0, splitk_su_bytes = 0;
-  bool dw_side() const { return su != sc; }
+  // Do the blocks' dW GEMMs run on the update stream, beside the next block's
+  // dX chain?  Where one launch of them is at most a round of 256 x 256 tiles
+  // on the 256 CUs, it fills the tails of the chain's kernels (GPT-2-small
+  // step 12.30 -> 11.88 ms, GPT-2-medium width 7.98 -> 7.74 ms); a launch of
+  // several rounds fills the chip by itself, and sharing it only costs (1.3B
+  // width 12.60 -> 12.94 ms).
+  bool dw_side() const {
+    const int64_t weights = 4 * (int64_t)cfg.d_model * cfg.d_model + 2 * (int64_t)cfg.d_model * cfg.d_ff;
+    return su != sc && cfg.model == LAYUP_MODEL_GPT_BF16 && weights <= 256 * 256 * 256;
+  }
   float* dis_partial = nullptr;
   // MLP
   std::vector<float*> mlp_act;  // input copy not kept: act[0] = x pointer of the step
@@ -221,8 +222,8 @@ struct layup_ctx {
 
 namespace {
 
-constexpr size_t SPLITK_BYTES = 256u << 20;  // room for an 8-way split of an 8192 x 768 float32 output
 constexpr size_t SPLITK_SU_BYTES = 128u << 20;  // split-K of the dW GEMMs on the update stream
+constexpr size_t SPLITK_BYTES = 256u << 20;  // room for an 8-way split of an 8192 x 768 float32 output
 
 size_t carve(layup_ctx* c, char* base) {
   Carver cv{base};
@@ -355,39 +356,61 @@ Gemm mk(bool ak, bool bk, int64_t M, int64_t N, int64_t K, const void* A, int64_
   return g;
 }
 
-// timed: one of a block's linear-layer backward GEMMs (dX or dW); with GEMM
-// timing on, HIP events on its stream bracket the launch (and its split-K sum)
-layup_status run_gemm(layup_ctx* c, Gemm g, hipStream_t s, const char* what, bool timed = false) {
-  const bool side = s != c->sc;  // the update stream has a split-K workspace of its own
-  g.splitk_ws = side ? c->splitk_su : c->splitk;
-  g.splitk_ws_bytes = side ? c->splitk_su_bytes : c->splitk_bytes;
-  std::string m = gemm_check(g, false);
-  if (!m.empty()) return fail(c, LAYUP_ERR_SHAPE, std::string(what) + ": " + m);
-  timed = timed && c->gemm_timing;
-  if (timed) {
-    if ((size_t)c->gt_used + 2 > c->gt_events.size()) {
-      hipEvent_t e[2];
-      if (hipEventCreate(&e[0]) != hipSuccess || hipEventCreate(&e[1]) != hipSuccess)
-        return fail(c, LAYUP_ERR_HIP, "event creation failed");
-      c->gt_events.push_back(e[0]);
-      c->gt_events.push_back(e[1]);
-    }
-    HIPCHK(c, hipEventRecord(c->gt_events[c->gt_used], s), "GEMM timing event");
-  }
-  HIPCHK(c, launch_gemm_bf16(g, s), what);
-  if (timed) {
-    HIPCHK(c, hipEventRecord(c->gt_events[c->gt_used + 1], s), "GEMM timing event");
-    c->gt_used += 2;
-    c->gt_flops += 2.0 * (double)g.M * (double)g.N * (double)g.K * g.batch;
-  }
-  return LAYUP_OK;
-}
-
 #define TRY(x)                         \
   do {                                 \
     layup_status st_ = (x);            \
     if (st_ != LAYUP_OK) return st_;   \
   } while (0)
+
+// HIP events around a launch (or a group launch of n GEMMs) for the optional timing
+layup_status timing_start(layup_ctx* c, hipStream_t s) {
+  if ((size_t)c->gt_used + 2 > c->gt_events.size()) {
+    hipEvent_t e[2];
+    if (hipEventCreate(&e[0]) != hipSuccess || hipEventCreate(&e[1]) != hipSuccess)
+      return fail(c, LAYUP_ERR_HIP, "event creation failed");
+    c->gt_events.push_back(e[0]);
+    c->gt_events.push_back(e[1]);
+  }
+  HIPCHK(c, hipEventRecord(c->gt_events[c->gt_used], s), "GEMM timing event");
+  return LAYUP_OK;
+}
+layup_status timing_stop(layup_ctx* c, const Gemm* g, int n, hipStream_t s) {
+  HIPCHK(c, hipEventRecord(c->gt_events[c->gt_used + 1], s), "GEMM timing event");
+  c->gt_used += 2;
+  c->gt_gemms += n;
+  for (int i = 0; i < n; ++i) c->gt_flops += 2.0 * (double)g[i].M * (double)g[i].N * (double)g[i].K * g[i].batch;
+  return LAYUP_OK;
+}
+
+// timed: one of a block's linear-layer backward GEMMs (dX or dW); with GEMM
+// timing on, HIP events on its stream bracket the launch (and its split-K sum)
+layup_status run_gemm(layup_ctx* c, Gemm g, const char* what, bool timed = false) {
+  const hipStream_t s = c->sc;
+  g.splitk_ws = c->splitk;
+  g.splitk_ws_bytes = c->splitk_bytes;
+  std::string m = gemm_check(g, false);
+  if (!m.empty()) return fail(c, LAYUP_ERR_SHAPE, std::string(what) + ": " + m);
+  timed = timed && c->gemm_timing;
+  if (timed) TRY(timing_start(c, s));
+  HIPCHK(c, launch_gemm_bf16(g, s), what);
+  if (timed) TRY(timing_stop(c, &g, 1, s));
+  return LAYUP_OK;
+}
+
+// The dW GEMMs (with their bias sums) of a block's linear layers, one launch.
+layup_status run_gemm_group(layup_ctx* c, Gemm* g, int n, hipStream_t s, const char* what) {
+  for (int i = 0; i < n; ++i) {
+    // each stream has its own workspace, of one size: the same plan on either
+    g[i].splitk_ws = s == c->sc ? c->splitk : c->splitk_su;
+    g[i].splitk_ws_bytes = c->splitk_su_bytes;
+    std::string m = gemm_check(g[i], false);
+    if (!m.empty()) return fail(c, LAYUP_ERR_SHAPE, std::string(what) + ": " + m);
+  }
+  if (c->gemm_timing) TRY(timing_start(c, s));
+  HIPCHK(c, launch_gemm_bf16_group(g, n, s), what);
+  if (c->gemm_timing) TRY(timing_stop(c, g, n, s));
+  return LAYUP_OK;
+}
 
 // ---------------------------------------------------------------- GPT
 layup_status gpt_forward(layup_ctx* c, const int32_t* tokens, float* loss_out) {
@@ -397,118 +420,77 @@ layup_status gpt_forward(layup_ctx* c, const int32_t* tokens, float* loss_out) {
                 dh = d / H, Vp = align64(g.vocab);
   const float scale = 1.0f / sqrtf((float)dh);
   Flat fl{c};
-  // The forward of sequences [b0, b0 + nb) on stream st, in three pieces
-  // (embedding, block l, final LayerNorm + head + loss).  With an update
-  // stream (idle during the forward) the batch is taken in two halves, the
-  // second there, and the two halves' pieces are enqueued alternately so
-  // that both streams have work from the start; every row's arithmetic is
-  // the same either way.
-  auto embed = [&](int64_t b0, int64_t nb, hipStream_t st) -> layup_status {
-    const int64_t r0 = b0 * T;
-    const int32_t* tk = tokens + b0 * (T + 1);
-    HIPCHK(c, launch_embed_fwd(tk, fl.p("wte"), fl.p("wpe"), c->acts[0].x + r0 * d, (int)nb, (int)T, (int)d,
-                               g.vocab, st), "embedding");
-    return LAYUP_OK;
-  };
-  auto block = [&](int l, int64_t b0, int64_t nb, hipStream_t st) -> layup_status {
-    const int64_t r0 = b0 * T, n = nb * T;
-    {
-      BlockActs& A = c->acts[l];
-      const std::string p = "h" + std::to_string(l) + ".";
-      float* x_next = ((l + 1 < g.n_layer) ? c->acts[l + 1].x : c->xL) + r0 * d;
-      bf16_t* qkv = A.qkv + r0 * 3 * d;
-      bf16_t* o = A.o + r0 * d;
-      HIPCHK(c, launch_layernorm_fwd(A.x + r0 * d, fl.p(p + "ln1.g"), fl.p(p + "ln1.b"), A.a + r0 * d,
-                                     A.mean1 + r0, A.rstd1 + r0, n, (int)d, st), "ln1");
-      Gemm q = mk(true, true, n, 3 * d, d, A.a + r0 * d, d, fl.w16(p + "qkv.w"), d, qkv, 3 * d, EPI_BF16);
-      q.bias = fl.p(p + "qkv.b");
-      TRY(run_gemm(c, q, st, "qkv forward"));
-      if (A.of) {
-        HIPCHK(c, launch_attention_fwd(qkv, A.lse + b0 * H * T, o, A.of + r0 * d, (int)nb, (int)H, (int)T,
-                                       (int)dh, scale, st), "attention");
-      } else {
-        // scores S[z] = Q_h K_h^T, z = b*H + h
-        float* S = c->S + b0 * H * T * T;
-        bf16_t* P = A.P + b0 * H * T * T;
-        Gemm sg = mk(true, true, T, T, dh, qkv, 3 * d, qkv + d, 3 * d, S, T, EPI_F32);
-        sg.batch = (int)(nb * H);
-        sg.inner = (int)H;
-        sg.a_outer = sg.b_outer = T * 3 * d;
-        sg.a_inner = sg.b_inner = dh;
-        sg.c_outer = H * T * T;
-        sg.c_inner = T * T;
-        sg.causal = CAUSAL_OUT_LOWER;
-        TRY(run_gemm(c, sg, st, "scores"));
-        HIPCHK(c, launch_softmax_fwd(S, P, nb * H, (int)T, scale, st), "softmax");
-        // o_h = P V_h
-        Gemm pv = mk(true, false, T, dh, T, P, T, qkv + 2 * d, 3 * d, o, d, EPI_BF16);
-        pv.batch = (int)(nb * H);
-        pv.inner = (int)H;
-        pv.a_outer = H * T * T;
-        pv.a_inner = T * T;
-        pv.b_outer = T * 3 * d;
-        pv.b_inner = dh;
-        pv.c_outer = T * d;
-        pv.c_inner = dh;
-        pv.causal = CAUSAL_A_LOWER;
-        TRY(run_gemm(c, pv, st, "attention output"));
-      }
-      Gemm pr = mk(true, true, n, d, d, o, d, fl.w16(p + "proj.w"), d, A.h + r0 * d, d, EPI_F32);
-      pr.bias = fl.p(p + "proj.b");
-      pr.aux = A.x + r0 * d;
-      TRY(run_gemm(c, pr, st, "proj forward"));
-      HIPCHK(c, launch_layernorm_fwd(A.h + r0 * d, fl.p(p + "ln2.g"), fl.p(p + "ln2.b"), A.a2 + r0 * d,
-                                     A.mean2 + r0, A.rstd2 + r0, n, (int)d, st), "ln2");
-      Gemm fc = mk(true, true, n, F, d, A.a2 + r0 * d, d, fl.w16(p + "fc.w"), d, A.f + r0 * F, F, EPI_GELU);
-      fc.bias = fl.p(p + "fc.b");
-      fc.C2 = A.gl + r0 * F;
-      TRY(run_gemm(c, fc, st, "fc forward"));
-      Gemm mp = mk(true, true, n, d, F, A.gl + r0 * F, F, fl.w16(p + "mproj.w"), F, x_next, d, EPI_F32);
-      mp.bias = fl.p(p + "mproj.b");
-      mp.aux = A.h + r0 * d;
-      TRY(run_gemm(c, mp, st, "mproj forward"));
-    }
-    return LAYUP_OK;
-  };
-  auto tail = [&](int64_t b0, int64_t nb, hipStream_t st) -> layup_status {
-    const int64_t r0 = b0 * T, n = nb * T;
-    const int32_t* tk = tokens + b0 * (T + 1);
-    HIPCHK(c, launch_layernorm_fwd(c->xL + r0 * d, fl.p("lnf.g"), fl.p("lnf.b"), c->xf + r0 * d, c->meanf + r0,
-                                   c->rstdf + r0, n, (int)d, st), "lnf");
-    Gemm hd = mk(true, true, n, Vp, d, c->xf + r0 * d, d, fl.w16("wte"), d, c->logits + r0 * Vp, Vp, EPI_BF16);
-    TRY(run_gemm(c, hd, st, "head forward"));
-    HIPCHK(c, launch_ce_fwd_bwd(c->logits + r0 * Vp, Vp, tk, (int)nb, (int)T, g.vocab, c->logits + r0 * Vp,
-                                c->loss_rows + r0, nullptr, st, N), "cross-entropy");
-    return LAYUP_OK;
-  };
-  const bool side = c->dw_side();
-  const hipStream_t s2 = side ? c->su : s;
-  // the update stream starts after everything the compute stream had done
-  // when the step started (the previous step's updates and backward)
-  if (side) HIPCHK(c, hipStreamWaitEvent(s2, c->ev_start, 0), "wait step start");
-  // one stream: the whole batch at once (half-size products are less efficient)
-  const int64_t nb0 = (side && B >= 2) ? B / 2 : B;
-  const bool two = nb0 < B;
-  TRY(embed(0, nb0, s));
-  if (two) TRY(embed(nb0, B - nb0, s2));
+  // One pass over the batch on the compute stream.  (Two half batches on the
+  // two streams were slower: 12.00 against 11.65 ms a GPT-2-small step,
+  // 13.38 against 12.77 ms at the 1.3B stack's width -- half-size products
+  // waste more than the overlap hides.)
+  HIPCHK(c, launch_embed_fwd(tokens, fl.p("wte"), fl.p("wpe"), c->acts[0].x, (int)B, (int)T, (int)d, g.vocab, s),
+         "embedding");
   for (int l = 0; l < g.n_layer; ++l) {
-    TRY(block(l, 0, nb0, s));
-    if (two) TRY(block(l, nb0, B - nb0, s2));
+    BlockActs& A = c->acts[l];
+    const std::string p = "h" + std::to_string(l) + ".";
+    float* x_next = (l + 1 < g.n_layer) ? c->acts[l + 1].x : c->xL;
+    HIPCHK(c, launch_layernorm_fwd(A.x, fl.p(p + "ln1.g"), fl.p(p + "ln1.b"), A.a, A.mean1, A.rstd1, N, (int)d, s),
+           "ln1");
+    Gemm q = mk(true, true, N, 3 * d, d, A.a, d, fl.w16(p + "qkv.w"), d, A.qkv, 3 * d, EPI_BF16);
+    q.bias = fl.p(p + "qkv.b");
+    TRY(run_gemm(c, q, "qkv forward"));
+    if (A.of) {
+      HIPCHK(c, launch_attention_fwd(A.qkv, A.lse, A.o, A.of, (int)B, (int)H, (int)T, (int)dh, scale, s),
+             "attention");
+    } else {
+      // scores S[z] = Q_h K_h^T, z = b*H + h
+      Gemm sg = mk(true, true, T, T, dh, A.qkv, 3 * d, A.qkv + d, 3 * d, c->S, T, EPI_F32);
+      sg.batch = (int)(B * H);
+      sg.inner = (int)H;
+      sg.a_outer = sg.b_outer = T * 3 * d;
+      sg.a_inner = sg.b_inner = dh;
+      sg.c_outer = H * T * T;
+      sg.c_inner = T * T;
+      sg.causal = CAUSAL_OUT_LOWER;
+      TRY(run_gemm(c, sg, "scores"));
+      HIPCHK(c, launch_softmax_fwd(c->S, A.P, B * H, (int)T, scale, s), "softmax");
+      // o_h = P V_h
+      Gemm pv = mk(true, false, T, dh, T, A.P, T, A.qkv + 2 * d, 3 * d, A.o, d, EPI_BF16);
+      pv.batch = (int)(B * H);
+      pv.inner = (int)H;
+      pv.a_outer = H * T * T;
+      pv.a_inner = T * T;
+      pv.b_outer = T * 3 * d;
+      pv.b_inner = dh;
+      pv.c_outer = T * d;
+      pv.c_inner = dh;
+      pv.causal = CAUSAL_A_LOWER;
+      TRY(run_gemm(c, pv, "attention output"));
+    }
+    Gemm pr = mk(true, true, N, d, d, A.o, d, fl.w16(p + "proj.w"), d, A.h, d, EPI_F32);
+    pr.bias = fl.p(p + "proj.b");
+    pr.aux = A.x;
+    TRY(run_gemm(c, pr, "proj forward"));
+    HIPCHK(c, launch_layernorm_fwd(A.h, fl.p(p + "ln2.g"), fl.p(p + "ln2.b"), A.a2, A.mean2, A.rstd2, N, (int)d, s),
+           "ln2");
+    Gemm fc = mk(true, true, N, F, d, A.a2, d, fl.w16(p + "fc.w"), d, A.f, F, EPI_GELU);
+    fc.bias = fl.p(p + "fc.b");
+    fc.C2 = A.gl;
+    TRY(run_gemm(c, fc, "fc forward"));
+    Gemm mp = mk(true, true, N, d, F, A.gl, F, fl.w16(p + "mproj.w"), F, x_next, d, EPI_F32);
+    mp.bias = fl.p(p + "mproj.b");
+    mp.aux = A.h;
+    TRY(run_gemm(c, mp, "mproj forward"));
   }
-  TRY(tail(0, nb0, s));
-  if (two) TRY(tail(nb0, B - nb0, s2));
-  if (side) {
-    HIPCHK(c, hipEventRecord(c->ev_fwd_half, s2), "record forward half");
-    HIPCHK(c, hipStreamWaitEvent(s, c->ev_fwd_half, 0), "wait forward half");
-  }
-  if (loss_out) HIPCHK(c, launch_row_mean(c->loss_rows, N, loss_out, s), "loss mean");
+  HIPCHK(c, launch_layernorm_fwd(c->xL, fl.p("lnf.g"), fl.p("lnf.b"), c->xf, c->meanf, c->rstdf, N, (int)d, s), "lnf");
+  TRY(run_gemm(c, mk(true, true, N, Vp, d, c->xf, d, fl.w16("wte"), d, c->logits, Vp, EPI_BF16), "head forward"));
+  HIPCHK(c, launch_ce_fwd_bwd(c->logits, Vp, tokens, (int)B, (int)T, g.vocab, c->logits, c->loss_rows, loss_out, s),
+         "cross-entropy");
   // the token positions sorted by token (for the embedding backward at the
   // end of the step): on the update stream, off the critical path (the
   // embedding backward waits for it); the previous step's embedding
   // backward, which read the list, finished before the step started
+  const bool side = c->su != c->sc;
+  if (side) HIPCHK(c, hipStreamWaitEvent(c->su, c->ev_start, 0), "wait step start");
   HIPCHK(c, launch_token_sort(tokens, (int)B, (int)T, g.vocab, nullptr, (int32_t*)c->sorted, nullptr,
-                              nullptr, nullptr, s2), "token sort");
-  if (side) HIPCHK(c, hipEventRecord(c->ev_sort, s2), "record token sort");
+                              nullptr, nullptr, c->su), "token sort");
+  if (side) HIPCHK(c, hipEventRecord(c->ev_sort, c->su), "record token sort");
   return LAYUP_OK;
 }
 
@@ -519,99 +501,49 @@ layup_status gpt_backward(layup_ctx* c, int u) {
                 dh = d / H, Vp = align64(g.vocab);
   const float scale = 1.0f / sqrtf((float)dh);
   Flat fl{c};
-  // dW GEMMs and bias sums go to the update stream when it is a different
-  // stream (sw); the events order them against the compute stream (s): an
-  // operand is read there only after s wrote it, and s overwrites it only
-  // after those reads (two blocks later, by parity)
-  const bool side = c->dw_side();
-  const hipStream_t sw = c->su;
-  auto rec = [&](hipEvent_t e, hipStream_t st) { return side ? hipEventRecord(e, st) : hipSuccess; };
-  auto wait = [&](hipStream_t st, hipEvent_t e) { return side ? hipStreamWaitEvent(st, e, 0) : hipSuccess; };
-  enum { OP_A = 0, OP_F = 1, OP_B = 2, OP_Q = 3 };
-  // The head's dW (the tied wte's gradient, needed only by the embedding
-  // backward at the very end).  With a separate update stream it runs there
-  // after the top block's dW GEMMs, filling that stream's slack instead of
-  // taking 0.7 ms of the compute stream (measured: 1 % faster steps; next to
-  // the head's dX, the two largest GEMMs of the step slowed each other, and
-  // four vocabulary slices of it were slower than one GEMM).
-  auto head_dw = [&](hipStream_t st) -> layup_status {
-    Gemm dw = mk(false, false, Vp, d, N, c->logits, Vp, c->xf, d, fl.g("wte"), d, EPI_F32);
-    return run_gemm(c, dw, st, "head dW");
-  };
   if (u == g.n_layer + 1) {
     // output head (tied wte) and final LayerNorm
     Gemm dx = mk(true, false, N, d, Vp, c->logits, Vp, fl.w16("wte"), d, c->da, d, EPI_F32);
-    TRY(run_gemm(c, dx, s, "head dX"));
-    if (!side) TRY(head_dw(s));
+    TRY(run_gemm(c, dx, "head dX"));
+    // the tied wte's gradient: the embedding backward adds the tokens' rows at the end
+    TRY(run_gemm(c, mk(false, false, Vp, d, N, c->logits, Vp, c->xf, d, fl.g("wte"), d, EPI_F32), "head dW"));
     c->cur_dx = 0;
-    const int q = (g.n_layer - 1) & 1;  // the last block's output-gradient operand
-    HIPCHK(c, wait(s, c->ev_rd[OP_A][q]), "wait operand free");
     HIPCHK(c, launch_layernorm_bwd(c->da, c->xL, c->meanf, c->rstdf, fl.p("lnf.g"), nullptr,
-                                   c->dx[0], c->dyA[q], c->ln_part, fl.g("lnf.g"), fl.g("lnf.b"), N,
+                                   c->dx[0], c->dyA[(g.n_layer - 1) & 1], c->ln_part, fl.g("lnf.g"), fl.g("lnf.b"), N,
                                    (int)d, s), "lnf backward");
-    return LAYUP_OK;  // the unit event orders dyA for the update stream
+    return LAYUP_OK;
   }
   if (u == 0) {
-    HIPCHK(c, wait(s, c->ev_head), "wait head dW");  // the embedding adds into the wte gradient
-    HIPCHK(c, wait(s, c->ev_sort), "wait token sort");
+    if (c->su != s) HIPCHK(c, hipStreamWaitEvent(s, c->ev_sort, 0), "wait token sort");
     HIPCHK(c, launch_embed_bwd(c->dx[c->cur_dx], (const int32_t*)c->sorted, fl.g("wte"), fl.g("wpe"),
                                (int)B, (int)T, (int)d, g.vocab, s), "embedding backward");
     return LAYUP_OK;
   }
   const int l = u - 1;
-  const int pq = l & 1;
   const BlockActs& A = c->acts[l];
   const std::string p = "h" + std::to_string(l) + ".";
   float* dxo = c->dx[c->cur_dx];
   float* dxi = c->dx[c->cur_dx ^ 1];
+  const int pq = l & 1;
+  const bool side = c->dw_side();
   bf16_t *dyA = c->dyA[pq], *df16 = c->dfb[pq], *dyB = c->dyB[pq], *dq16 = c->dqb[pq];
-  // Every linear layer: dX on the compute stream (the critical path), then
-  // dW and db.  In the fused schedule the dW GEMM updates the weight in
-  // place, so it must follow the layer's dX (which reads the weight first):
-  // the MLP output projection's dW is issued after the event that follows
-  // the MLP's dX GEMMs (ev_mid) and the attention projection's after the
-  // unit event, the same events the other dW GEMMs wait for (an extra event
-  // record per layer on the compute stream costs it a few microseconds of
-  // idle time each).
-  const bool fz = c->fused_dw;
-  // The bias gradient (column sums of dY) comes out of the same dW GEMM: its
-  // A operand is dY^T, whose row sums it accumulates from the fragments.
-  auto weight_grads = [&](int op, Gemm dw, const std::string& wname, const char* bname,
-                          const char* what) -> layup_status {
-    dw.rowsum = fl.g(p + bname);
-    TRY(run_gemm(c, dw_gemm(c, dw, wname), sw, what, true));
-    HIPCHK(c, rec(c->ev_rd[op][pq], sw), "record operand read");
-    return LAYUP_OK;
-  };
+  // The dX chain on the compute stream (the critical path), then the four dW
+  // products (and bias gradients, the row sums of their A operand dY^T) in
+  // one launch, on the update stream or here (dw_side).  In the fused
+  // schedule they update the weights in place, after the chain has read them.
+  // One launch of all four needs no split-K to fill the chip: 4 x 45 us and
+  // four sums of 8 us became 144 us per GPT-2-small block.
   // MLP output projection: dY = dyA (written by the LayerNorm backward that produced dxo)
   Gemm dg = mk(true, false, N, F, d, dyA, d, fl.w16(p + "mproj.w"), F, df16, F, EPI_DGELU);
   dg.aux = A.f;
-  HIPCHK(c, wait(s, c->ev_rd[OP_F][pq]), "wait operand free");
-  TRY(run_gemm(c, dg, s, "mproj dX + gelu backward", true));
-  // dyA was written before the previous unit event, which the update stream
-  // has waited for
-  const Gemm mproj_dw = mk(false, false, d, F, N, dyA, d, A.gl, F, fl.g(p + "mproj.w"), F, EPI_F32);
-  if (!fz) TRY(weight_grads(OP_A, mproj_dw, p + "mproj.w", "mproj.b", "mproj dW + db"));
+  TRY(run_gemm(c, dg, "mproj dX + gelu backward", true));
   // MLP input projection: dY = df16
-  Gemm fcx = mk(true, false, N, d, F, df16, F, fl.w16(p + "fc.w"), d, c->da, d, EPI_F32);
-  TRY(run_gemm(c, fcx, s, "fc dX", true));
-  HIPCHK(c, wait(s, c->ev_rd[OP_B][pq]), "wait operand free");
+  TRY(run_gemm(c, mk(true, false, N, d, F, df16, F, fl.w16(p + "fc.w"), d, c->da, d, EPI_F32), "fc dX", true));
   HIPCHK(c, launch_layernorm_bwd(c->da, A.h, A.mean2, A.rstd2, fl.p(p + "ln2.g"), dxo, c->dh,
                                  dyB, c->ln_part, fl.g(p + "ln2.g"), fl.g(p + "ln2.b"), N, (int)d,
                                  s), "ln2 backward");
-  // one event for df16 and dyB (each event record on the compute stream
-  // costs a few microseconds of idle time there)
-  HIPCHK(c, rec(c->ev_mid[pq], s), "record operands written");
-  HIPCHK(c, wait(sw, c->ev_mid[pq]), "wait operands written");
-  if (fz) TRY(weight_grads(OP_A, mproj_dw, p + "mproj.w", "mproj.b", "mproj dW + db"));
-  TRY(weight_grads(OP_F, mk(false, false, F, d, N, df16, F, A.a2, d, fl.g(p + "fc.w"), d, EPI_F32),
-                   p + "fc.w", "fc.b", "fc dW + db"));
   // attention output projection: dY = dyB = bf16(dh) from the LayerNorm backward above
-  Gemm prx = mk(true, false, N, d, d, dyB, d, fl.w16(p + "proj.w"), d, c->do16, d, EPI_BF16);
-  TRY(run_gemm(c, prx, s, "proj dX", true));
-  const Gemm proj_dw = mk(false, false, d, d, N, dyB, d, A.o, d, fl.g(p + "proj.w"), d, EPI_F32);
-  if (!fz) TRY(weight_grads(OP_B, proj_dw, p + "proj.w", "proj.b", "proj dW + db"));
-  HIPCHK(c, wait(s, c->ev_rd[OP_Q][pq]), "wait operand free");
+  TRY(run_gemm(c, mk(true, false, N, d, d, dyB, d, fl.w16(p + "proj.w"), d, c->do16, d, EPI_BF16), "proj dX", true));
   if (A.of) {
     // attention core, fused: dQ, dK, dV from recomputed scores (P and dS stay
     // in registers)
@@ -635,42 +567,41 @@ layup_status gpt_backward(layup_ctx* c, int u) {
     const int64_t TT = T * T;
     // dP = dO_h V_h^T
     TRY(run_gemm(c, batched(mk(true, true, T, T, dh, c->do16, d, A.qkv + 2 * d, 3 * d, c->S, T, EPI_F32),
-                            T * d, dh, T * 3 * d, dh, H * TT, TT, CAUSAL_OUT_LOWER), s, "dP"));
+                            T * d, dh, T * 3 * d, dh, H * TT, TT, CAUSAL_OUT_LOWER), "dP"));
     // dV_h = P^T dO_h
     TRY(run_gemm(c, batched(mk(false, false, T, dh, T, A.P, T, c->do16, d, dq16 + 2 * d, 3 * d,
-                               EPI_BF16), H * TT, TT, T * d, dh, T * 3 * d, dh, CAUSAL_A_UPPER), s, "dV"));
+                               EPI_BF16), H * TT, TT, T * d, dh, T * 3 * d, dh, CAUSAL_A_UPPER), "dV"));
     HIPCHK(c, launch_softmax_bwd(c->S, A.P, c->dS, B * H, (int)T, scale, s), "softmax backward");
     // dQ_h = dS K_h
     TRY(run_gemm(c, batched(mk(true, false, T, dh, T, c->dS, T, A.qkv + d, 3 * d, dq16, 3 * d,
-                               EPI_BF16), H * TT, TT, T * 3 * d, dh, T * 3 * d, dh, CAUSAL_A_LOWER), s, "dQ"));
+                               EPI_BF16), H * TT, TT, T * 3 * d, dh, T * 3 * d, dh, CAUSAL_A_LOWER), "dQ"));
     // dK_h = dS^T Q_h
     TRY(run_gemm(c, batched(mk(false, false, T, dh, T, c->dS, T, A.qkv, 3 * d, dq16 + d, 3 * d,
-                               EPI_BF16), H * TT, TT, T * 3 * d, dh, T * 3 * d, dh, CAUSAL_A_UPPER), s, "dK"));
+                               EPI_BF16), H * TT, TT, T * 3 * d, dh, T * 3 * d, dh, CAUSAL_A_UPPER), "dK"));
   }
   // qkv projection: dY = dq16
-  Gemm qx = mk(true, false, N, d, 3 * d, dq16, 3 * d, fl.w16(p + "qkv.w"), d, c->da, d, EPI_F32);
-  TRY(run_gemm(c, qx, s, "qkv dX", true));
+  TRY(run_gemm(c, mk(true, false, N, d, 3 * d, dq16, 3 * d, fl.w16(p + "qkv.w"), d, c->da, d, EPI_F32), "qkv dX", true));
+  auto dw = [&](int64_t M, int64_t Nn, const bf16_t* dy, const bf16_t* x, const char* w, const char* b) {
+    Gemm g2 = mk(false, false, M, Nn, N, dy, M, x, Nn, fl.g(p + w), Nn, EPI_F32);
+    g2.rowsum = fl.g(p + b);
+    return dw_gemm(c, g2, p + w);
+  };
+  Gemm dws[4] = {dw(3 * d, d, dq16, A.a, "qkv.w", "qkv.b"), dw(d, d, dyB, A.o, "proj.w", "proj.b"),
+                 dw(F, d, df16, A.a2, "fc.w", "fc.b"), dw(d, F, dyA, A.gl, "mproj.w", "mproj.b")};
+  if (!side) TRY(run_gemm_group(c, dws, 4, s, "block dW + db"));
+  // the next block's operands were last read by the dW GEMMs of the block
+  // before this one; one wait a block covers them all
+  if (side) HIPCHK(c, hipStreamWaitEvent(s, c->ev_rd[pq ^ 1], 0), "wait operands free");
   // LayerNorm 1; its bf16 dx is the next block's output-gradient operand
-  const int nq = pq ^ 1;
-  if (l > 0) HIPCHK(c, wait(s, c->ev_rd[OP_A][nq]), "wait operand free");
   HIPCHK(c, launch_layernorm_bwd(c->da, A.x, A.mean1, A.rstd1, fl.p(p + "ln1.g"), c->dh, dxi,
-                                 l > 0 ? c->dyA[nq] : nullptr, c->ln_part, fl.g(p + "ln1.g"),
+                                 l > 0 ? c->dyA[pq ^ 1] : nullptr, c->ln_part, fl.g(p + "ln1.g"),
                                  fl.g(p + "ln1.b"), N, (int)d,
                                  s), "ln1 backward");
   if (side) {
-    // the unit event (compute stream's part of the unit done) also orders
-    // dq16 and the next block's dyA for the update stream; the qkv dW GEMM
-    // follows it there, ahead of the unit's update
     HIPCHK(c, hipEventRecord(c->ev_unit[u], s), "record unit event");
-    HIPCHK(c, hipStreamWaitEvent(sw, c->ev_unit[u], 0), "wait unit event");
-    c->unit_recorded = true;
-  }
-  if (fz) TRY(weight_grads(OP_B, proj_dw, p + "proj.w", "proj.b", "proj dW + db"));
-  TRY(weight_grads(OP_Q, mk(false, false, 3 * d, d, N, dq16, 3 * d, A.a, d, fl.g(p + "qkv.w"), d, EPI_F32),
-                   p + "qkv.w", "qkv.b", "qkv dW + db"));
-  if (side && l == (int)g.n_layer - 1) {
-    TRY(head_dw(sw));
-    HIPCHK(c, rec(c->ev_head, sw), "record head dW done");
+    HIPCHK(c, hipStreamWaitEvent(c->su, c->ev_unit[u], 0), "wait unit event");
+    TRY(run_gemm_group(c, dws, 4, c->su, "block dW + db"));
+    HIPCHK(c, hipEventRecord(c->ev_rd[pq], c->su), "record operands read");
   }
   c->cur_dx ^= 1;
   return LAYUP_OK;
@@ -1019,16 +950,9 @@ layup_status layup_init(layup_ctx** out, const layup_config* cfg, const layup_bu
     layup_destroy(c);
     return fail(nullptr, LAYUP_ERR_HIP, "event creation failed");
   }
-  // ordering events between the compute stream and the update stream's dW work
-  bool ev_ok = hipEventCreateWithFlags(&c->ev_head, hipEventDisableTiming) == hipSuccess &&
-          hipEventCreateWithFlags(&c->ev_sort, hipEventDisableTiming) == hipSuccess &&
-          hipEventCreateWithFlags(&c->ev_fwd_half, hipEventDisableTiming) == hipSuccess;
-  for (int q = 0; q < 2; ++q) {
-    ev_ok = ev_ok && hipEventCreateWithFlags(&c->ev_mid[q], hipEventDisableTiming) == hipSuccess;
-    for (int k = 0; k < 4; ++k)
-      ev_ok = ev_ok && hipEventCreateWithFlags(&c->ev_rd[k][q], hipEventDisableTiming) == hipSuccess;
-  }
-  if (!ev_ok) {
+  if (hipEventCreateWithFlags(&c->ev_sort, hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&c->ev_rd[0], hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&c->ev_rd[1], hipEventDisableTiming) != hipSuccess) {
     layup_destroy(c);
     return fail(nullptr, LAYUP_ERR_HIP, "event creation failed");
   }
@@ -1046,14 +970,9 @@ void layup_destroy(layup_ctx* ctx) {
   if (ctx->ev_start) hipEventDestroy(ctx->ev_start);
   if (ctx->ev_fwd_end) hipEventDestroy(ctx->ev_fwd_end);
   if (ctx->ev_join) hipEventDestroy(ctx->ev_join);
-  for (auto e : ctx->ev_mid)
-    if (e) hipEventDestroy(e);
-  for (auto& row : ctx->ev_rd)
-    for (auto e : row)
-      if (e) hipEventDestroy(e);
-  if (ctx->ev_head) hipEventDestroy(ctx->ev_head);
   if (ctx->ev_sort) hipEventDestroy(ctx->ev_sort);
-  if (ctx->ev_fwd_half) hipEventDestroy(ctx->ev_fwd_half);
+  for (auto e : ctx->ev_rd)
+    if (e) hipEventDestroy(e);
   delete ctx;
 }
 
@@ -1100,14 +1019,15 @@ layup_status layup_layer_backward(layup_ctx* ctx, int32_t unit) {
   if (unit != ctx->next_backward)
     return fail(ctx, LAYUP_ERR_STATE, "units must be backpropagated in reverse order, expected " +
                                           std::to_string(ctx->next_backward));
-  ctx->unit_recorded = false;
   layup_status st = ctx->cfg.model == LAYUP_MODEL_GPT_BF16 ? gpt_backward(ctx, unit) : mlp_backward(ctx, unit);
   if (st != LAYUP_OK) return st;
-  if (!ctx->unit_recorded) HIPCHK(ctx, hipEventRecord(ctx->ev_unit[unit], ctx->sc), "record unit event");
-  if (ctx->dw_side()) {
-    // the unit's gradients are complete once both streams' parts are: the
-    // event is re-recorded on the update stream behind the compute stream's
-    HIPCHK(ctx, hipStreamWaitEvent(ctx->su, ctx->ev_unit[unit], 0), "wait unit event");
+  // The unit's gradient is complete where its last GEMM ran: a block's on the
+  // update stream (which has waited for the compute stream's part), and the
+  // embeddings', the last one produced, behind the bottom block's there.
+  const bool on_su = ctx->dw_side() && unit <= ctx->cfg.n_layer;
+  if (!on_su || unit == 0) HIPCHK(ctx, hipEventRecord(ctx->ev_unit[unit], ctx->sc), "record unit event");
+  if (on_su) {
+    if (unit == 0) HIPCHK(ctx, hipStreamWaitEvent(ctx->su, ctx->ev_unit[unit], 0), "wait unit event");
     HIPCHK(ctx, hipEventRecord(ctx->ev_unit[unit], ctx->su), "record unit event");
   }
   ctx->backward_done[unit] = 1;
@@ -1306,7 +1226,7 @@ layup_status layup_gemm_timing(layup_ctx* ctx, int32_t enable) {
   if (!ctx) return fail(nullptr, LAYUP_ERR_INVALID_ARG, "null context");
   TRY(layup_synchronize(ctx));
   ctx->gemm_timing = enable != 0;
-  ctx->gt_used = 0;
+  ctx->gt_used = ctx->gt_gemms = 0;
   ctx->gt_flops = 0.0;
   return LAYUP_OK;
 }
@@ -1321,7 +1241,7 @@ layup_status layup_gemm_timing_read(layup_ctx* ctx, float* total_ms, int32_t* la
     tot += ms;
   }
   *total_ms = tot;
-  *launches = ctx->gt_used / 2;
+  *launches = ctx->gt_gemms;
   *flops = ctx->gt_flops;
   return LAYUP_OK;
 }
