@@ -214,9 +214,7 @@ hipError_t launch_row_mean(const float* x, int64_t n, float* out, hipStream_t s)
 hipError_t launch_f32_to_bf16(const float* x, bf16_t* y, int64_t n, hipStream_t s);
 hipError_t launch_embed_bwd(const float* dx, const int32_t* sorted_pos, float* dwte, float* dwpe,
                             int B, int T, int d, int V, hipStream_t s);
-hipError_t launch_token_sort(const int32_t* tokens, int B, int T, int V, int32_t* counts,
-                             int32_t* sorted_pos, int32_t* seg_start, int32_t* seg_token,
-                             int32_t* n_seg, hipStream_t s);
+hipError_t launch_token_sort(const int32_t* tokens, int B, int T, int V, int32_t* sorted_pos, hipStream_t s);
 hipError_t launch_ce_f32(const float* logits, const int32_t* labels, int rows, int V,
                          float* dlogits, float* loss_rows, float* loss_out, hipStream_t s);
 

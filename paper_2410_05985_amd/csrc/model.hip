@@ -488,8 +488,7 @@ layup_status gpt_forward(layup_ctx* c, const int32_t* tokens, float* loss_out) {
   // backward, which read the list, finished before the step started
   const bool side = c->su != c->sc;
   if (side) HIPCHK(c, hipStreamWaitEvent(c->su, c->ev_start, 0), "wait step start");
-  HIPCHK(c, launch_token_sort(tokens, (int)B, (int)T, g.vocab, nullptr, (int32_t*)c->sorted, nullptr,
-                              nullptr, nullptr, c->su), "token sort");
+  HIPCHK(c, launch_token_sort(tokens, (int)B, (int)T, g.vocab, (int32_t*)c->sorted, c->su), "token sort");
   if (side) HIPCHK(c, hipEventRecord(c->ev_sort, c->su), "record token sort");
   return LAYUP_OK;
 }
