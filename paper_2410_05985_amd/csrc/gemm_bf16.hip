@@ -677,20 +677,21 @@ __device__ __forceinline__ void gemm_item(const KArgs& P, int lid) {
 }
 
 // The logical work item of a hardware workgroup.  The grid is one dimension
-// of work items, padded to a multiple of 8.  Workgroups are dealt round-robin
+// of n work items, padded to a multiple of 8.  Workgroups are dealt round-robin
 // over the 8 XCDs (each with its own L2), so hardware id h runs on XCD h % 8:
 // the remap gives every XCD a contiguous range of logical ids, i.e. whole
 // bands of tiles of one batch/split that share operand rows.
-__device__ __forceinline__ int work_item() {
+__device__ __forceinline__ int work_item(int n) {
   const int h = blockIdx.x;
-  return (h & 7) * (int)(gridDim.x >> 3) + (h >> 3);
+  return (h & 7) * ((n + 7) >> 3) + (h >> 3);
 }
 
 // OCC: workgroups per CU.
 template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, bool AK, bool BKM, int EPI, bool SPLIT, int BKV>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_kernel(const KArgs P) {
-  const int lid = work_item();
-  if (lid >= P.tiles_m * P.tiles_n * (SPLIT ? P.splits : P.nz)) return;
+  const int n = P.tiles_m * P.tiles_n * (SPLIT ? P.splits : P.nz);
+  const int lid = work_item(n);
+  if (lid >= n) return;
   gemm_item<BM, BN, WGM, WGN, STAGES, AK, BKM, EPI, SPLIT, BKV>(P, lid);
 }
 
@@ -701,13 +702,26 @@ struct GroupArgs {
   int32_t n;
   int32_t first[MAX_GROUP + 1];   // first work item of each product
   int32_t rfirst[MAX_GROUP + 1];  // first workgroup of each product's split-K sum
+  int32_t n_ln, ln_blocks;        // LayerNorm gradient sums riding along: blocks of each
+  LnSum ln[2];
   KArgs p[MAX_GROUP];
 };
 
 template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool SPLIT, int BKV>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_group_kernel(const GroupArgs G) {
-  const int lid = work_item();
-  if (lid >= G.first[G.n]) return;
+  const int n = G.first[G.n], ng = (n + 7) / 8 * 8;
+  if ((int)blockIdx.x >= ng) {
+    // the LayerNorm sums follow the products: they run on the CUs the last round leaves free
+    constexpr int NT = 64 * WGM * WGN;
+    static_assert(NT % LN_SUM_THREADS == 0, "whole teams of the LayerNorm sum");
+    __shared__ f32x4 red[NT];
+    const int b = (int)blockIdx.x - ng, sub = (int)threadIdx.x / LN_SUM_THREADS;
+    ln_sum_item(G.ln[b / G.ln_blocks], (b % G.ln_blocks) * (NT / LN_SUM_THREADS) + sub,
+                (int)threadIdx.x % LN_SUM_THREADS, red + sub * LN_SUM_THREADS);
+    return;
+  }
+  const int lid = work_item(n);
+  if (lid >= n) return;
   int i = 0;
   while (i + 1 < G.n && lid >= G.first[i + 1]) ++i;
   gemm_item<BM, BN, WGM, WGN, STAGES, false, false, EPI, SPLIT, BKV>(G.p[i], lid - G.first[i]);
@@ -935,23 +949,26 @@ std::string gemm_check(const Gemm& g, bool f32_operands) {
 struct TileCfg {
   int bm, bn, occ;
   float step_lo, step_hi, fix;
+  float dw;  // steps of dW = dY^T X (both operands m-major, twice the LDS reads) take this much longer
 };
 enum TileId { T256x256 = 0, T256x192, T256x128, T128x192, T128x128, T128x64, T64x64, kNumCfg };
 static const TileCfg kCfgs[kNumCfg] = {
-    {256, 256, 1, 1.30f, 1.75f, 3.0f},  // 2x4 waves (each 128x64), 2 stages of K 64
-    {256, 192, 1, 1.25f, 1.55f, 3.0f},  // 4x2 waves (each 64x96),  2 stages of K 64
-    {256, 128, 1, 0.85f, 1.10f, 3.0f},  // 4x2 waves (each 64x64),  3 stages of K 64
-    {128, 192, 1, 0.70f, 0.90f, 3.0f},  // 4x2 waves (each 32x96),  3 stages of K 64
-    {128, 128, 2, 0.70f, 1.15f, 3.0f},  // 2x4 waves (each 64x32),  2 stages of K 64
-    {128, 64, 3, 0.41f, 1.10f, 2.5f},   // 2x2 waves (each 64x32),  4 stages of K 32
-    {64, 64, 4, 0.38f, 0.72f, 2.0f},    // 2x2 waves (each 32x32),  2 stages of K 64
+    {256, 256, 1, 1.30f, 1.75f, 3.0f, 1.12f},  // 2x4 waves (each 128x64), 2 stages of K 64
+    {256, 192, 1, 1.25f, 1.55f, 3.0f, 1.12f},  // 4x2 waves (each 64x96),  2 stages of K 64
+    {256, 128, 1, 0.85f, 1.10f, 3.0f, 1.05f},  // 4x2 waves (each 64x64),  3 stages of K 64
+    {128, 192, 1, 0.70f, 0.90f, 3.0f, 1.12f},  // 4x2 waves (each 32x96),  3 stages of K 64
+    {128, 128, 2, 0.70f, 1.15f, 3.0f, 1.12f},  // 2x4 waves (each 64x32),  2 stages of K 64
+    {128, 64, 3, 0.41f, 1.10f, 2.5f, 1.12f},   // 2x2 waves (each 64x32),  4 stages of K 32
+    {64, 64, 4, 0.38f, 0.72f, 2.0f, 1.12f},    // 2x2 waves (each 32x32),  2 stages of K 64
 };
 
 namespace {
 template <int BM, int BN, int WGM, int WGN, int STG, int OCC, int BKV, int EPI>
-hipError_t launch_group_epi(const GroupArgs& G, bool split, hipStream_t s) {
-  const dim3 grid((unsigned)((G.first[G.n] + 7) / 8 * 8));
+hipError_t launch_group_epi(const GroupArgs& G0, bool split, hipStream_t s) {
   constexpr int NT = 64 * WGM * WGN;
+  GroupArgs G = G0;
+  if (G.n_ln) G.ln_blocks = (int)cdiv(ln_sum_teams(G.ln[0].d), NT / LN_SUM_THREADS);
+  const dim3 grid((unsigned)((G.first[G.n] + 7) / 8 * 8 + G.n_ln * G.ln_blocks));
   if (!split) {
     gemm_bf16_group_kernel<BM, BN, WGM, WGN, STG, OCC, EPI, false, BKV><<<grid, NT, 0, s>>>(G);
     return hipGetLastError();
@@ -972,11 +989,15 @@ hipError_t launch_group(const GroupArgs& G, int epi, bool split, hipStream_t s) 
 
 // The products share K, the epilogue (float32 or the weight update) and the
 // split-K workspace, which splits > 1 needs room in for all of them.
-hipError_t launch_gemm_bf16_group_cfg(const Gemm* g, int n, int cfg, int splits, hipStream_t s) {
+hipError_t launch_gemm_bf16_group_cfg(const Gemm* g, int n, const LnSum* ln, int n_ln, int cfg, int splits,
+                                      hipStream_t s) {
+  if (n_ln < 0 || n_ln > 2 || (n_ln == 2 && ln[0].d != ln[1].d)) return hipErrorInvalidValue;
   if (n < 1 || n > MAX_GROUP || cfg < 0 || cfg >= kNumCfg) return hipErrorInvalidValue;
   GroupArgs G;
   memset(&G, 0, sizeof(G));
   G.n = n;
+  G.n_ln = n_ln;
+  for (int i = 0; i < n_ln; ++i) G.ln[i] = ln[i];
   const int BM = kCfgs[cfg].bm, BN = kCfgs[cfg].bn;
   const int64_t K = g[0].K;
   size_t per_split = 0;
@@ -1060,7 +1081,7 @@ static float est_items(const TileCfg& t, int64_t items, float steps, float bytes
   // workgroups that share a CU hide part of it behind the next round's products
   const float epi = bytes * t.bm * t.bn * t.occ / 25e3f;
   const float round = steps * t.step_hi + t.fix + epi * (t.occ > 1 ? 0.6f : 1.0f);
-  const int64_t full = items / slots, rest = items % slots;
+  const int64_t full = (items - 1) / slots, rest = items - full * slots;  // rest: the last round, 1..slots
   float us = full * round;
   if (rest > 0) {
     // the last round takes as long as its fullest CU (one workgroup per CU:
@@ -1098,8 +1119,7 @@ static Plan choose(const Gemm* g, int n, bool group) {
     for (int i = 0; i < n; ++i) tiles += cdiv(g[i].M, t.bm) * cdiv(g[i].N, t.bn) * g[i].batch;
     for (int sp = 1; sp <= std::max<int64_t>(1, max_split); ++sp) {
       if (sp > 1 && (sp * per_split > g[0].splitk_ws_bytes || g[0].M > 65535)) break;
-      // an m-major A (dW) is read with twice the LDS reads: steps take an eighth longer
-      const float steps = (float)cdiv(cdiv(g[0].K, sp), 64) * (g[0].a_kmajor ? 1.0f : 1.12f);
+      const float steps = (float)cdiv(cdiv(g[0].K, sp), 64) * (g[0].a_kmajor ? 1.0f : t.dw);
       float us = est_items(t, tiles * sp, steps, sp > 1 ? 4.f : bytes);
       if (sp > 1) us += 8.f + (float)(outputs * (4.0 * sp + bytes) / 4.5e6);
       if (us < best_us) {
@@ -1111,9 +1131,9 @@ static Plan choose(const Gemm* g, int n, bool group) {
   return best;
 }
 
-hipError_t launch_gemm_bf16_group(const Gemm* g, int n, hipStream_t s) {
+hipError_t launch_gemm_bf16_group(const Gemm* g, int n, const LnSum* ln, int n_ln, hipStream_t s) {
   const Plan p = choose(g, n, true);
-  return launch_gemm_bf16_group_cfg(g, n, p.cfg, p.splits, s);
+  return launch_gemm_bf16_group_cfg(g, n, ln, n_ln, p.cfg, p.splits, s);
 }
 
 hipError_t launch_gemm_bf16(const Gemm& g, hipStream_t s) {

@@ -424,36 +424,9 @@ __global__ __launch_bounds__(64 * LN_WAVES) void layernorm_bwd_kernel(
   }
 }
 
-// dg | db = the nb partial rows [nb][2d] summed in a fixed order.  A block
-// covers 16 columns (4 float4 groups) with 64 row lanes: lane l adds rows l,
-// l+64, ... in order (all of its loads in flight at once for nb <= 256), then
-// the 64 lane sums are added pairwise in a fixed tree (lane l += lane l+h for
-// h = 32, 16, ..., 1).  96 blocks for d = 768, so the pass is one memory
-// round trip rather than a serial walk down the partial rows.
-constexpr int LNP_COLS = 4;    // float4 column groups per block
-constexpr int LNP_LANES = 64;  // row lanes per block
-__global__ __launch_bounds__(LNP_COLS * LNP_LANES) void ln_partial_sum_kernel(const float* part, int64_t nb,
-                                                                               int d, float* dg, float* db) {
-  __shared__ f32x4 red[LNP_LANES][LNP_COLS];
-  const int cg = threadIdx.x % LNP_COLS, rl = threadIdx.x / LNP_COLS;
-  const int64_t cols = 2 * (int64_t)d;
-  const int64_t c = ((int64_t)blockIdx.x * LNP_COLS + cg) * 4;
-  f32x4 s{0.f, 0.f, 0.f, 0.f};
-  if (c < cols) {
-#pragma unroll 4
-    for (int64_t r = rl; r < nb; r += LNP_LANES) s += *reinterpret_cast<const f32x4*>(part + r * cols + c);
-  }
-  red[rl][cg] = s;
-  __syncthreads();
-#pragma unroll
-  for (int h = LNP_LANES / 2; h >= 1; h >>= 1) {
-    if (rl < h) red[rl][cg] += red[rl + h][cg];
-    __syncthreads();
-  }
-  if (rl == 0 && c < cols) {
-    float* out = c < d ? dg + c : db + (c - d);
-    *reinterpret_cast<f32x4*>(out) = red[0][cg];
-  }
+__global__ __launch_bounds__(LN_SUM_THREADS) void ln_partial_sum_kernel(const LnSum L) {
+  __shared__ f32x4 red[LN_SUM_THREADS];
+  ln_sum_item(L, (int)blockIdx.x, (int)threadIdx.x, red);
 }
 
 template <int NVL>
@@ -481,10 +454,13 @@ hipError_t launch_layernorm_bwd(const float* dy, const float* x, const float* me
   else if (nvl == 3) e = ln_bwd_launch<3>(dy, x, mean, rstd, g, dres, dx, dx16, part, rows, d, nb, s);
   else if (nvl == 4) e = ln_bwd_launch<4>(dy, x, mean, rstd, g, dres, dx, dx16, part, rows, d, nb, s);
   else e = ln_bwd_launch<8>(dy, x, mean, rstd, g, dres, dx, dx16, part, rows, d, nb, s);
-  if (e != hipSuccess) return e;
-  ln_partial_sum_kernel<<<(unsigned)cdiv(2 * (int64_t)d, 4 * LNP_COLS), LNP_COLS * LNP_LANES, 0, s>>>(part, nb, d, dg,
-                                                                                                 db);
+  if (e != hipSuccess || !dg) return e;
+  ln_partial_sum_kernel<<<(unsigned)ln_sum_teams(d), LN_SUM_THREADS, 0, s>>>(layernorm_sum(part, dg, db, rows, d));
   return hipGetLastError();
+}
+
+LnSum layernorm_sum(const float* part, float* dg, float* db, int64_t rows, int d) {
+  return LnSum{part, dg, db, cdiv(rows, LN_ROWS), d, 0};
 }
 
 // ------------------------------------------------------- causal softmax

@@ -167,10 +167,50 @@ enum Causal : int { CAUSAL_NONE = 0, CAUSAL_OUT_LOWER = 1, CAUSAL_A_LOWER = 2, C
 // Validates shapes/alignment; returns a message or empty string.
 std::string gemm_check(const Gemm& g, bool f32_operands);
 hipError_t launch_gemm_bf16(const Gemm& g, hipStream_t stream);
+// Sum of the LayerNorm backward's per-block partial rows [nb][2 d] into dg and
+// db, in a fixed order.  A team of LN_SUM_THREADS threads covers 16 columns
+// (4 float4 groups) with 64 row lanes: lane l adds rows l, l+64, ... in order
+// (all of its loads in flight at once for nb <= 256), then the 64 lane sums
+// are added pairwise in a fixed tree (lane l += lane l+h for h = 32, 16, ...,
+// 1).  96 teams for d = 768, so the pass is one memory round trip rather than
+// a serial walk down the partial rows.
+struct LnSum {
+  const float* part;
+  float* dg;
+  float* db;
+  int64_t nb;
+  int32_t d, pad;
+};
+constexpr int LN_SUM_COLS = 4;    // float4 column groups per team
+constexpr int LN_SUM_LANES = 64;  // row lanes per team
+constexpr int LN_SUM_THREADS = LN_SUM_COLS * LN_SUM_LANES;
+inline int64_t ln_sum_teams(int64_t d) { return cdiv(2 * d, 4 * LN_SUM_COLS); }
+// Thread tid of team `team`; red: LN_SUM_THREADS entries of LDS per team.
+// Every thread of the workgroup calls it (barriers).
+__device__ __forceinline__ void ln_sum_item(const LnSum& L, int team, int tid, f32x4* red) {
+  const int cg = tid % LN_SUM_COLS, rl = tid / LN_SUM_COLS;
+  const int64_t cols = 2 * (int64_t)L.d;
+  const int64_t c = ((int64_t)team * LN_SUM_COLS + cg) * 4;
+  f32x4 s{0.f, 0.f, 0.f, 0.f};
+  if (c < cols) {
+#pragma unroll 4
+    for (int64_t r = rl; r < L.nb; r += LN_SUM_LANES) s += *reinterpret_cast<const f32x4*>(L.part + r * cols + c);
+  }
+  red[rl * LN_SUM_COLS + cg] = s;
+  __syncthreads();
+#pragma unroll
+  for (int h = LN_SUM_LANES / 2; h >= 1; h >>= 1) {
+    if (rl < h) red[rl * LN_SUM_COLS + cg] += red[(rl + h) * LN_SUM_COLS + cg];
+    __syncthreads();
+  }
+  if (rl == 0 && c < cols) *reinterpret_cast<f32x4*>(c < L.d ? L.dg + c : L.db + (c - L.d)) = red[cg];
+}
+
 // Up to four products dW = dY^T X of the same K and epilogue (float32 or the
 // weight update; batch 1) in one launch; the split-K workspace is g[0]'s.
+// Up to two LayerNorm gradient sums (of one width) ride along.
 constexpr int GEMM_GROUP_MAX = 4;
-hipError_t launch_gemm_bf16_group(const Gemm* g, int n, hipStream_t stream);
+hipError_t launch_gemm_bf16_group(const Gemm* g, int n, const LnSum* ln, int n_ln, hipStream_t stream);
 hipError_t launch_gemm_f32(const Gemm& g, hipStream_t stream);
 
 // ------------------------------------------------------------ glue kernels
@@ -180,8 +220,11 @@ hipError_t launch_layernorm_fwd(const float* x, const float* g, const float* b, 
                                 float* mean, float* rstd, int64_t rows, int d, hipStream_t s);
 // LayerNorm backward: dx (float32) and optionally its bfloat16 copy dx16;
 // per-block partial sums of dg and db go to part
-// (layernorm_bwd_partial_floats(rows, d) floats) and are added into dg, db
-// in a fixed order.  d a multiple of 4, at most 2048.
+// (layernorm_bwd_partial_floats(rows, d) floats) and are summed into dg, db
+// by a second launch, or, with dg null, by the caller (layernorm_sum).
+// d a multiple of 4, at most 2048.
+struct LnSum;
+LnSum layernorm_sum(const float* part, float* dg, float* db, int64_t rows, int d);
 int64_t layernorm_bwd_partial_floats(int64_t rows, int d);
 hipError_t launch_layernorm_bwd(const float* dy, const float* x, const float* mean,
                                 const float* rstd, const float* g, const float* dres,

@@ -198,7 +198,7 @@ struct layup_ctx {
   bf16_t *dyA[2] = {}, *dfb[2] = {}, *dyB[2] = {}, *dqb[2] = {};
   hipEvent_t ev_rd[2] = {};      // dW GEMMs of block parity q done (update stream)
   hipEvent_t ev_sort = nullptr;  // the token sort done (update stream)
-  float* ln_part = nullptr;
+  float* ln_part[2][2] = {};  // LayerNorm backward's partial rows: [block parity][ln1, ln2]
   float *splitk = nullptr, *splitk_su = nullptr;
   size_t splitk_bytes = 0, splitk_su_bytes = 0;
   // Do the blocks' dW GEMMs run on the update stream, beside the next block's
@@ -272,7 +272,8 @@ size_t carve(layup_ctx* c, char* base) {
       c->dqb[q] = cv.take<bf16_t>(N * 3 * d);
     }
     c->do16 = cv.take<bf16_t>(N * d);
-    c->ln_part = cv.take<float>(layernorm_bwd_partial_floats(N, (int)d));
+    for (auto& q : c->ln_part)
+      for (auto& x : q) x = cv.take<float>(layernorm_bwd_partial_floats(N, (int)d));
     c->splitk = cv.take<float>(SPLITK_BYTES / 4);
     c->splitk_bytes = SPLITK_BYTES;
     c->splitk_su = cv.take<float>(SPLITK_SU_BYTES / 4);
@@ -398,7 +399,7 @@ layup_status run_gemm(layup_ctx* c, Gemm g, const char* what, bool timed = false
 }
 
 // The dW GEMMs (with their bias sums) of a block's linear layers, one launch.
-layup_status run_gemm_group(layup_ctx* c, Gemm* g, int n, hipStream_t s, const char* what) {
+layup_status run_gemm_group(layup_ctx* c, Gemm* g, int n, const LnSum* ln, int n_ln, hipStream_t s, const char* what) {
   for (int i = 0; i < n; ++i) {
     // each stream has its own workspace, of one size: the same plan on either
     g[i].splitk_ws = s == c->sc ? c->splitk : c->splitk_su;
@@ -407,7 +408,7 @@ layup_status run_gemm_group(layup_ctx* c, Gemm* g, int n, hipStream_t s, const c
     if (!m.empty()) return fail(c, LAYUP_ERR_SHAPE, std::string(what) + ": " + m);
   }
   if (c->gemm_timing) TRY(timing_start(c, s));
-  HIPCHK(c, launch_gemm_bf16_group(g, n, s), what);
+  HIPCHK(c, launch_gemm_bf16_group(g, n, ln, n_ln, s), what);
   if (c->gemm_timing) TRY(timing_stop(c, g, n, s));
   return LAYUP_OK;
 }
@@ -508,7 +509,7 @@ layup_status gpt_backward(layup_ctx* c, int u) {
     TRY(run_gemm(c, mk(false, false, Vp, d, N, c->logits, Vp, c->xf, d, fl.g("wte"), d, EPI_F32), "head dW"));
     c->cur_dx = 0;
     HIPCHK(c, launch_layernorm_bwd(c->da, c->xL, c->meanf, c->rstdf, fl.p("lnf.g"), nullptr,
-                                   c->dx[0], c->dyA[(g.n_layer - 1) & 1], c->ln_part, fl.g("lnf.g"), fl.g("lnf.b"), N,
+                                   c->dx[0], c->dyA[(g.n_layer - 1) & 1], c->ln_part[g.n_layer & 1][0], fl.g("lnf.g"), fl.g("lnf.b"), N,
                                    (int)d, s), "lnf backward");
     return LAYUP_OK;
   }
@@ -539,8 +540,7 @@ layup_status gpt_backward(layup_ctx* c, int u) {
   // MLP input projection: dY = df16
   TRY(run_gemm(c, mk(true, false, N, d, F, df16, F, fl.w16(p + "fc.w"), d, c->da, d, EPI_F32), "fc dX", true));
   HIPCHK(c, launch_layernorm_bwd(c->da, A.h, A.mean2, A.rstd2, fl.p(p + "ln2.g"), dxo, c->dh,
-                                 dyB, c->ln_part, fl.g(p + "ln2.g"), fl.g(p + "ln2.b"), N, (int)d,
-                                 s), "ln2 backward");
+                                 dyB, c->ln_part[pq][1], nullptr, nullptr, N, (int)d, s), "ln2 backward");
   // attention output projection: dY = dyB = bf16(dh) from the LayerNorm backward above
   TRY(run_gemm(c, mk(true, false, N, d, d, dyB, d, fl.w16(p + "proj.w"), d, c->do16, d, EPI_BF16), "proj dX", true));
   if (A.of) {
@@ -587,21 +587,23 @@ layup_status gpt_backward(layup_ctx* c, int u) {
   };
   Gemm dws[4] = {dw(3 * d, d, dq16, A.a, "qkv.w", "qkv.b"), dw(d, d, dyB, A.o, "proj.w", "proj.b"),
                  dw(F, d, df16, A.a2, "fc.w", "fc.b"), dw(d, F, dyA, A.gl, "mproj.w", "mproj.b")};
-  if (!side) TRY(run_gemm_group(c, dws, 4, s, "block dW + db"));
-  // the next block's operands were last read by the dW GEMMs of the block
-  // before this one; one wait a block covers them all
+  // the LayerNorms' gradient sums ride along (a launch of their own each took
+  // 5 us, 24 a GPT-2-small step)
+  const LnSum sums[2] = {layernorm_sum(c->ln_part[pq][0], fl.g(p + "ln1.g"), fl.g(p + "ln1.b"), N, (int)d),
+                         layernorm_sum(c->ln_part[pq][1], fl.g(p + "ln2.g"), fl.g(p + "ln2.b"), N, (int)d)};
+  // the next block's operands (and partial rows) were last read by the dW
+  // launch of the block before this one; one wait a block covers them all
   if (side) HIPCHK(c, hipStreamWaitEvent(s, c->ev_rd[pq ^ 1], 0), "wait operands free");
   // LayerNorm 1; its bf16 dx is the next block's output-gradient operand
   HIPCHK(c, launch_layernorm_bwd(c->da, A.x, A.mean1, A.rstd1, fl.p(p + "ln1.g"), c->dh, dxi,
-                                 l > 0 ? c->dyA[pq ^ 1] : nullptr, c->ln_part, fl.g(p + "ln1.g"),
-                                 fl.g(p + "ln1.b"), N, (int)d,
-                                 s), "ln1 backward");
+                                 l > 0 ? c->dyA[pq ^ 1] : nullptr, c->ln_part[pq][0], nullptr, nullptr, N, (int)d, s),
+         "ln1 backward");
   if (side) {
     HIPCHK(c, hipEventRecord(c->ev_unit[u], s), "record unit event");
     HIPCHK(c, hipStreamWaitEvent(c->su, c->ev_unit[u], 0), "wait unit event");
-    TRY(run_gemm_group(c, dws, 4, c->su, "block dW + db"));
-    HIPCHK(c, hipEventRecord(c->ev_rd[pq], c->su), "record operands read");
   }
+  TRY(run_gemm_group(c, dws, 4, sums, 2, side ? c->su : s, "block dW + db"));
+  if (side) HIPCHK(c, hipEventRecord(c->ev_rd[pq], c->su), "record operands read");
   c->cur_dx ^= 1;
   return LAYUP_OK;
 }
