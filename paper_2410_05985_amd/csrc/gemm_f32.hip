@@ -44,13 +44,13 @@ __device__ __forceinline__ f32x4 load4(const float* p, int64_t ld, int64_t r, in
 // the four k of group l / 16; instruction e multiplies the k 4 g + e of the
 // four groups g, the same set for both operands.
 template <bool AK, bool BKM, int T, int NW>
-__global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const F32Args P) {
+__device__ __forceinline__ void gemm_f32_tile(const F32Args& P, int bx, int by) {
   constexpr int UN = T == 1 ? 4 : 2;  // K chunks in flight
   __shared__ float red[NW > 1 ? NW : 1][T * T][4][64];
   __shared__ float rred[NW][T][16];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int g = lane >> 4, r16 = lane & 15;
-  const int64_t m0 = (int64_t)blockIdx.y * (16 * T), n0 = (int64_t)blockIdx.x * (16 * T);
+  const int64_t m0 = (int64_t)by * (16 * T), n0 = (int64_t)bx * (16 * T);
   int64_t ar[T], br[T];
 #pragma unroll
   for (int i = 0; i < T; ++i) {
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const F32Args P) {
       for (int i = 0; i < T; ++i) rs[i] += (a[u][i][0] + a[u][i][1]) + (a[u][i][2] + a[u][i][3]);
     }
   }
-  const bool rowsum = P.rowsum && blockIdx.x == 0;
+  const bool rowsum = P.rowsum && bx == 0;
   if (rowsum) {
 #pragma unroll
     for (int i = 0; i < T; ++i) {
@@ -133,6 +133,24 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const F32Args P) {
   }
 }
 
+template <bool AK, bool BKM, int T, int NW>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const F32Args P) {
+  gemm_f32_tile<AK, BKM, T, NW>(P, blockIdx.x, blockIdx.y);
+}
+
+// dW and dX of a layer: the first workgroups take dW's 16 x 16 tiles, the
+// others dX's, row by row.
+struct F32Pair {
+  F32Args dw, dx;
+  int32_t dw_n, dw_items, dx_n, pad;  // tile columns of each, tiles of dW
+};
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_backward_kernel(const F32Pair P) {
+  const int b = blockIdx.x;
+  if (b < P.dw_items) gemm_f32_tile<false, false, 1, NW>(P.dw, b % P.dw_n, b / P.dw_n);
+  else gemm_f32_tile<true, false, 1, NW>(P.dx, (b - P.dw_items) % P.dx_n, (b - P.dw_items) / P.dx_n);
+}
+
 template <int T, int NW>
 hipError_t launch_tile(const Gemm& g, const F32Args& P, hipStream_t s) {
   const int64_t gy = cdiv(P.M, 16 * T);
@@ -162,9 +180,7 @@ hipError_t launch_tile(const Gemm& g, const F32Args& P, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_gemm_f32(const Gemm& g, hipStream_t s) {
-  if (g.M == 0 || g.N == 0) return hipSuccess;
-  if (g.batch != 1) return hipErrorInvalidValue;
+static F32Args f32_args(const Gemm& g) {
   F32Args P;
   P.A = (const float*)g.A;
   P.B = (const float*)g.B;
@@ -182,13 +198,37 @@ hipError_t launch_gemm_f32(const Gemm& g, hipStream_t s) {
   P.relu = g.relu;
   P.vec_a = g.lda % 4 == 0 && ((uintptr_t)g.A & 15) == 0;
   P.vec_b = g.ldb % 4 == 0 && ((uintptr_t)g.B & 15) == 0;
-  // 16 x 16 tiles while they do not fill the chip a few times over (each of
-  // the 256 CUs holds four 8-wave workgroups); beyond that 32 x 32 tiles read
-  // each operand half as often.  Eight waves where K gives each of them more
-  // than one chunk, two for the short K of dW (the batch).
-  const int64_t t16 = cdiv(g.M, 16) * cdiv(g.N, 16);
-  if (t16 > 4096) return g.K > 64 ? launch_tile<2, 4>(g, P, s) : launch_tile<2, 1>(g, P, s);
+  return P;
+}
+
+// 16 x 16 tiles while they do not fill the chip a few times over (each of
+// the 256 CUs holds four 8-wave workgroups); beyond that 32 x 32 tiles read
+// each operand half as often.
+constexpr int64_t F32_SMALL_TILES = 4096;
+static int64_t tiles16(const Gemm& g) { return cdiv(g.M, 16) * cdiv(g.N, 16); }
+
+hipError_t launch_gemm_f32(const Gemm& g, hipStream_t s) {
+  if (g.M == 0 || g.N == 0) return hipSuccess;
+  if (g.batch != 1) return hipErrorInvalidValue;
+  const F32Args P = f32_args(g);
+  // eight (four) waves where K gives each of them more than one chunk, two
+  // (one) for the short K of dW (the batch)
+  if (tiles16(g) > F32_SMALL_TILES) return g.K > 64 ? launch_tile<2, 4>(g, P, s) : launch_tile<2, 1>(g, P, s);
   return g.K > 64 ? launch_tile<1, 8>(g, P, s) : launch_tile<1, 2>(g, P, s);
+}
+
+// A launch costs more than either product of the tiny MLP's layers (4 us), so
+// the pair shares one while both stay on small tiles.
+hipError_t launch_gemm_f32_backward(const Gemm& dw, const Gemm& dx, hipStream_t s) {
+  const int64_t a = tiles16(dw), b = tiles16(dx);
+  if (a < 1 || b < 1 || a + b > F32_SMALL_TILES || dw.batch != 1 || dx.batch != 1 || dw.a_kmajor || dw.b_kmajor ||
+      !dx.a_kmajor || dx.b_kmajor) {
+    const hipError_t e = launch_gemm_f32(dw, s);
+    return e != hipSuccess ? e : launch_gemm_f32(dx, s);
+  }
+  const F32Pair P{f32_args(dw), f32_args(dx), (int)cdiv(dw.N, 16), (int)a, (int)cdiv(dx.N, 16), 0};
+  gemm_f32_backward_kernel<8><<<(unsigned)(a + b), 512, 0, s>>>(P);
+  return hipGetLastError();
 }
 
 }  // namespace layup

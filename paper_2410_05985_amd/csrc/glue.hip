@@ -784,11 +784,8 @@ hipError_t launch_row_mean(const float* x, int64_t n, float* out, hipStream_t s)
 
 // float32 logits [rows, V] with labels: loss = mean(lse - z[y]),
 // dz = (softmax - onehot) / rows.  One wave64 per row.
-__global__ void ce_f32_kernel(const float* z, const int32_t* labels, int rows, int V, float* dz,
-                              float* loss_rows) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
+__device__ __forceinline__ float ce_f32_row(const float* z, const int32_t* labels, int row, int rows, int V,
+                                            float* dz, int lane) {
   const float* zr = z + (int64_t)row * V;
   float mx = -INFINITY;
   for (int j = lane; j < V; j += 64) mx = fmaxf(mx, zr[j]);
@@ -800,11 +797,41 @@ __global__ void ce_f32_kernel(const float* z, const int32_t* labels, int rows, i
   const bool valid = y >= 0 && y < V;  // an invalid label adds no loss and no gradient
   for (int j = lane; j < V; j += 64)
     dz[(int64_t)row * V + j] = valid ? (expf(zr[j] - mx) / s - (j == y ? 1.f : 0.f)) / (float)rows : 0.f;
-  if (lane == 0) loss_rows[row] = valid ? logf(s) + mx - zr[y] : 0.f;
+  return valid ? logf(s) + mx - zr[y] : 0.f;
+}
+
+__global__ void ce_f32_kernel(const float* z, const int32_t* labels, int rows, int V, float* dz,
+                              float* loss_rows) {
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  const float loss = ce_f32_row(z, labels, row, rows, V, dz, lane);
+  if (lane == 0) loss_rows[row] = loss;
+}
+
+// The same with the mean in one workgroup, for few rows (two a wave): the
+// second launch costs more than the rows.
+constexpr int CE_F32_ONE = 32;
+__global__ __launch_bounds__(1024) void ce_f32_mean_kernel(const float* z, const int32_t* labels, int rows, int V,
+                                                           float* dz, float* loss_rows, float* loss_out) {
+  __shared__ float loss[CE_F32_ONE];
+  const int lane = threadIdx.x & 63;
+  for (int row = threadIdx.x >> 6; row < rows; row += 16) {
+    const float x = ce_f32_row(z, labels, row, rows, V, dz, lane);
+    if (lane == 0) loss[row] = loss_rows[row] = x;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const float s = warp_sum(lane < rows ? loss[lane] : 0.f);
+  if (lane == 0) *loss_out = s / (float)rows;
 }
 
 hipError_t launch_ce_f32(const float* logits, const int32_t* labels, int rows, int V, float* dlogits,
                          float* loss_rows, float* loss_out, hipStream_t s) {
+  if (loss_out && rows <= CE_F32_ONE) {
+    ce_f32_mean_kernel<<<1, 1024, 0, s>>>(logits, labels, rows, V, dlogits, loss_rows, loss_out);
+    return hipGetLastError();
+  }
   ce_f32_kernel<<<(unsigned)cdiv(rows, 4), 256, 0, s>>>(logits, labels, rows, V, dlogits, loss_rows);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !loss_out) return e;

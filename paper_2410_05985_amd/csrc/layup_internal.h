@@ -212,6 +212,8 @@ __device__ __forceinline__ void ln_sum_item(const LnSum& L, int team, int tid, f
 constexpr int GEMM_GROUP_MAX = 4;
 hipError_t launch_gemm_bf16_group(const Gemm* g, int n, const LnSum* ln, int n_ln, hipStream_t stream);
 hipError_t launch_gemm_f32(const Gemm& g, hipStream_t stream);
+// dW (m-major operands) and dX (k-major A) of one linear layer, in one launch where both are small
+hipError_t launch_gemm_f32_backward(const Gemm& dw, const Gemm& dx, hipStream_t stream);
 
 // ------------------------------------------------------------ glue kernels
 hipError_t launch_embed_fwd(const int32_t* tokens, const float* wte, const float* wpe, float* x,

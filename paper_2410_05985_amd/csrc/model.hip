@@ -17,6 +17,7 @@
 // Activations saved by the forward, gradient scratch and split-K partials
 // live in one caller-owned workspace carved by the context.
 #include <mutex>
+#include <unordered_map>
 #include <vector>
 
 #include "layup_internal.h"
@@ -35,6 +36,7 @@ struct TensorInfo {
 
 struct Layout {
   std::vector<TensorInfo> t;
+  std::unordered_map<std::string, int> index;  // by name
   int n_units = 0;
   int64_t total = 0;
   std::vector<std::vector<int>> unit_tensors;
@@ -78,6 +80,7 @@ Layout build_layout(const layup_config& c) {
     ti.decay = decay;
     ti.off = L.total;
     L.total = align64(L.total + (int64_t)ti.padded_rows * cols);
+    L.index.emplace(n, (int)L.t.size());
     L.t.push_back(ti);
   };
   if (c.model == LAYUP_MODEL_MLP_F32) {
@@ -149,10 +152,10 @@ struct layup_ctx {
   layup_buffers buf;
   hipStream_t sc = nullptr, su = nullptr;
   std::vector<hipEvent_t> ev_unit;     // gradient of unit u ready (compute stream)
+  std::vector<hipStream_t> unit_on;    // stream ev_unit was last recorded on
   std::vector<hipEvent_t> ev_applied;  // update+mix of unit u done (update stream)
   hipEvent_t ev_start = nullptr;       // start of the step's forward pass
   hipEvent_t ev_fwd_end = nullptr;     // end of the forward pass (loss gradient formed)
-  hipEvent_t ev_join = nullptr;
   bool timeline_valid = false;
   // fused dW update (schedule LAYUP_SCHEDULE_FUSED_DW) of the step in flight
   bool fused_dw = false;
@@ -164,7 +167,8 @@ struct layup_ctx {
   std::vector<hipEvent_t> gt_events;  // start/stop pairs
   int gt_used = 0, gt_gemms = 0;      // events used, GEMMs they cover
   double gt_flops = 0.0;
-  bool have_join = false;
+  bool have_join = false;  // a step's last update is recorded (ev_applied[0]) ...
+  bool joined = false;     // ... and the compute stream has waited for it
   std::string err;
   int device = 0;
   // state machine of one step
@@ -196,7 +200,6 @@ struct layup_ctx {
   //   dyB: the gradient after the attention residual (attention projection)
   //   dqb: dQ, dK, dV (qkv projection)
   bf16_t *dyA[2] = {}, *dfb[2] = {}, *dyB[2] = {}, *dqb[2] = {};
-  hipEvent_t ev_rd[2] = {};      // dW GEMMs of block parity q done (update stream)
   hipEvent_t ev_sort = nullptr;  // the token sort done (update stream)
   float* ln_part[2][2] = {};  // LayerNorm backward's partial rows: [block parity][ln1, ln2]
   float *splitk = nullptr, *splitk_su = nullptr;
@@ -308,10 +311,17 @@ layup_status hip_fail(layup_ctx* c, hipError_t e, const char* what) {
     if (e_ != hipSuccess) return hip_fail(c, e_, what); \
   } while (0)
 
+// The compute stream waits for the last step's last update (once a step).
+hipError_t wait_join(layup_ctx* c) {
+  if (!c->have_join || c->joined) return hipSuccess;
+  const hipError_t e = hipStreamWaitEvent(c->sc, c->ev_applied[0], 0);
+  c->joined = e == hipSuccess;
+  return e;
+}
+
 const TensorInfo* find(const layup_ctx* c, const std::string& n) {
-  for (const auto& t : c->L.t)
-    if (t.name == n) return &t;
-  return nullptr;
+  const auto it = c->L.index.find(n);
+  return it == c->L.index.end() ? nullptr : &c->L.t[it->second];
 }
 
 // pointers into the flat buffers
@@ -593,7 +603,8 @@ layup_status gpt_backward(layup_ctx* c, int u) {
                          layernorm_sum(c->ln_part[pq][1], fl.g(p + "ln2.g"), fl.g(p + "ln2.b"), N, (int)d)};
   // the next block's operands (and partial rows) were last read by the dW
   // launch of the block before this one; one wait a block covers them all
-  if (side) HIPCHK(c, hipStreamWaitEvent(s, c->ev_rd[pq ^ 1], 0), "wait operands free");
+  // (its unit's event follows it on the update stream)
+  if (side && l + 1 < (int)g.n_layer) HIPCHK(c, hipStreamWaitEvent(s, c->ev_unit[u + 1], 0), "wait operands free");
   // LayerNorm 1; its bf16 dx is the next block's output-gradient operand
   HIPCHK(c, launch_layernorm_bwd(c->da, A.x, A.mean1, A.rstd1, fl.p(p + "ln1.g"), c->dh, dxi,
                                  l > 0 ? c->dyA[pq ^ 1] : nullptr, c->ln_part[pq][0], nullptr, nullptr, N, (int)d, s),
@@ -603,7 +614,6 @@ layup_status gpt_backward(layup_ctx* c, int u) {
     HIPCHK(c, hipStreamWaitEvent(c->su, c->ev_unit[u], 0), "wait unit event");
   }
   TRY(run_gemm_group(c, dws, 4, sums, 2, side ? c->su : s, "block dW + db"));
-  if (side) HIPCHK(c, hipEventRecord(c->ev_rd[pq], c->su), "record operands read");
   c->cur_dx ^= 1;
   return LAYUP_OK;
 }
@@ -642,14 +652,19 @@ layup_status mlp_backward(layup_ctx* c, int u) {
   Flat fl{c};
   const std::string p = "fc" + std::to_string(u + 1) + ".";
   const float* hin = u == 0 ? c->mlp_x : c->mlp_act[u];
-  // db (column sums of dz) comes out of the dW product, the ReLU's gradient out of dX
-  Gemm dw = mk(false, false, out, in, Bt, c->mlp_dz, out, hin, in, fl.g(p + "w"), in, EPI_F32);
-  dw.rowsum = fl.g(p + "b");
-  TRY(mlp_gemm(c, dw, "mlp dW + db"));
-  if (u > 0) {
-    Gemm dx = mk(true, false, Bt, in, out, c->mlp_dz, out, fl.p(p + "w"), in, c->mlp_dh, in, EPI_F32);
-    dx.mask = c->mlp_act[u];
-    TRY(mlp_gemm(c, dx, "mlp dX"));
+  // dW with db (column sums of dz), and dX with the ReLU's gradient: one launch
+  Gemm g2[2];
+  g2[0] = mk(false, false, out, in, Bt, c->mlp_dz, out, hin, in, fl.g(p + "w"), in, EPI_F32);
+  g2[0].rowsum = fl.g(p + "b");
+  if (u == 0) return mlp_gemm(c, g2[0], "mlp dW + db");
+  g2[1] = mk(true, false, Bt, in, out, c->mlp_dz, out, fl.p(p + "w"), in, c->mlp_dh, in, EPI_F32);
+  g2[1].mask = c->mlp_act[u];
+  for (const Gemm& x : g2) {
+    const std::string m = gemm_check(x, true);
+    if (!m.empty()) return fail(c, LAYUP_ERR_SHAPE, "mlp backward: " + m);
+  }
+  HIPCHK(c, launch_gemm_f32_backward(g2[0], g2[1], c->sc), "mlp dW + db, dX");
+  {
     std::swap(c->mlp_dz, c->mlp_dh);
   }
   return LAYUP_OK;
@@ -706,7 +721,8 @@ layup_status unit_update(layup_ctx* c, int u, const layup_hparams* hp, float alp
   if (!c->backward_done[u]) return fail(c, LAYUP_ERR_STATE, "unit updated before its backward");
   std::vector<UMTensor> ts;
   unit_tensors(c, u, peer, peer16, ts);
-  HIPCHK(c, hipStreamWaitEvent(c->su, c->ev_unit[u], 0), "wait for unit gradient");
+  // (recorded on the update stream itself, the event needs no wait there)
+  if (c->unit_on[u] != c->su) HIPCHK(c, hipStreamWaitEvent(c->su, c->ev_unit[u], 0), "wait for unit gradient");
   TraceInfo tr;
   tr.trace = c->buf.trace;
   tr.counter = c->buf.trace_counter;
@@ -724,8 +740,8 @@ layup_status unit_update(layup_ctx* c, int u, const layup_hparams* hp, float alp
   HIPCHK(c, hipEventRecord(c->ev_applied[u], c->su), "record unit applied");
   c->backward_done[u] = 0;
   if (u == 0) {
-    HIPCHK(c, hipEventRecord(c->ev_join, c->su), "record join");
-    c->have_join = true;
+    c->have_join = true;  // ev_applied[0] joins the streams
+    c->joined = c->su == c->sc;
     c->timeline_valid = true;
     c->step_index++;
   }
@@ -939,6 +955,7 @@ layup_status layup_init(layup_ctx** out, const layup_config* cfg, const layup_bu
   c->ev_unit.assign(c->L.n_units, nullptr);
   c->ev_applied.assign(c->L.n_units, nullptr);
   c->backward_done.assign(c->L.n_units, 0);
+  c->unit_on.assign(c->L.n_units, nullptr);
   // unit events carry timestamps (the per-unit timeline); the join does not
   for (int u = 0; u < c->L.n_units; ++u) {
     if (hipEventCreate(&c->ev_unit[u]) != hipSuccess || hipEventCreate(&c->ev_applied[u]) != hipSuccess) {
@@ -946,14 +963,11 @@ layup_status layup_init(layup_ctx** out, const layup_config* cfg, const layup_bu
       return fail(nullptr, LAYUP_ERR_HIP, "event creation failed");
     }
   }
-  if (hipEventCreate(&c->ev_start) != hipSuccess || hipEventCreate(&c->ev_fwd_end) != hipSuccess ||
-      hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming) != hipSuccess) {
+  if (hipEventCreate(&c->ev_start) != hipSuccess || hipEventCreate(&c->ev_fwd_end) != hipSuccess) {
     layup_destroy(c);
     return fail(nullptr, LAYUP_ERR_HIP, "event creation failed");
   }
-  if (hipEventCreateWithFlags(&c->ev_sort, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&c->ev_rd[0], hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&c->ev_rd[1], hipEventDisableTiming) != hipSuccess) {
+  if (hipEventCreateWithFlags(&c->ev_sort, hipEventDisableTiming) != hipSuccess) {
     layup_destroy(c);
     return fail(nullptr, LAYUP_ERR_HIP, "event creation failed");
   }
@@ -970,10 +984,7 @@ void layup_destroy(layup_ctx* ctx) {
   for (auto e : ctx->gt_events) hipEventDestroy(e);
   if (ctx->ev_start) hipEventDestroy(ctx->ev_start);
   if (ctx->ev_fwd_end) hipEventDestroy(ctx->ev_fwd_end);
-  if (ctx->ev_join) hipEventDestroy(ctx->ev_join);
   if (ctx->ev_sort) hipEventDestroy(ctx->ev_sort);
-  for (auto e : ctx->ev_rd)
-    if (e) hipEventDestroy(e);
   delete ctx;
 }
 
@@ -987,7 +998,7 @@ layup_status layup_synchronize(layup_ctx* ctx) {
 layup_status layup_refresh_shadow(layup_ctx* ctx) {
   if (!ctx) return fail(nullptr, LAYUP_ERR_INVALID_ARG, "null context");
   if (!ctx->buf.params_bf16) return LAYUP_OK;
-  if (ctx->have_join) HIPCHK(ctx, hipStreamWaitEvent(ctx->sc, ctx->ev_join, 0), "wait join");
+  HIPCHK(ctx, wait_join(ctx), "wait join");
   HIPCHK(ctx, launch_f32_to_bf16(ctx->buf.params, ctx->buf.params_bf16, ctx->L.total, ctx->sc),
          "bf16 copy");
   return LAYUP_OK;
@@ -1000,7 +1011,7 @@ layup_status layup_forward(layup_ctx* ctx, const int32_t* tokens, const float* x
   for (char b : ctx->backward_done)
     if (b) return fail(ctx, LAYUP_ERR_STATE, "forward called while a unit awaits its update");
   // the forward reads every unit's weights: wait for the previous step's updates
-  if (ctx->have_join) HIPCHK(ctx, hipStreamWaitEvent(ctx->sc, ctx->ev_join, 0), "wait join");
+  HIPCHK(ctx, wait_join(ctx), "wait join");
   HIPCHK(ctx, hipEventRecord(ctx->ev_start, ctx->sc), "record step start");
   ctx->timeline_valid = false;
   ctx->dx_valid = false;
@@ -1031,6 +1042,7 @@ layup_status layup_layer_backward(layup_ctx* ctx, int32_t unit) {
     if (unit == 0) HIPCHK(ctx, hipStreamWaitEvent(ctx->su, ctx->ev_unit[unit], 0), "wait unit event");
     HIPCHK(ctx, hipEventRecord(ctx->ev_unit[unit], ctx->su), "record unit event");
   }
+  ctx->unit_on[unit] = on_su ? ctx->su : ctx->sc;
   ctx->backward_done[unit] = 1;
   ctx->dx_valid = ctx->cfg.model == LAYUP_MODEL_GPT_BF16 && unit >= 1;
   ctx->next_backward--;
@@ -1191,7 +1203,7 @@ layup_status layup_step_ex(layup_ctx* ctx, const layup_step_args* a) {
     for (int u = U - 1; u >= 0; --u) TRY(unit_update(ctx, u, a->hp, a->alpha, peer, peer16, push, dis(u)));
   }
   // join: the compute stream continues only after the last update
-  HIPCHK(ctx, hipStreamWaitEvent(ctx->sc, ctx->ev_join, 0), "join");
+  HIPCHK(ctx, wait_join(ctx), "join");
   return LAYUP_OK;
 }
 

@@ -131,21 +131,23 @@ def test_update_mix_teacher_forced_two_steps(cfg):
     m.close()
 
 
-def test_embedding_backward_long_runs():
-    """Runs of one token at the edges of the scatter's grouping (4 waves of 8
-    rows in flight): 1, 31, 32, 33 and 700 positions of one token, the rest
-    drawn, and tokens outside the vocabulary (no row).  dwte = the head's
-    part + the run's rows, dwpe = the sum over the batch: float32 sums of at
-    most 701 terms in any order, each within 701 * 2^-24 (1.01 for higher
-    orders) of the exact sum times the sum of absolute values."""
-    cfg = S.GPT_TEST_LONG
+@pytest.mark.parametrize("batch,seq", [(2, 8), (1, 1024), (3, 344), (4, 512), (4, 1024), (3, 1368), (8, 1024)])
+def test_embedding_backward_long_runs(batch, seq):
+    """Token counts at the edges of the sort's 1, 2, 4 and 8 keys a thread, and
+    runs of one token at the edges of the scatter's grouping (4 waves of 8
+    rows in flight): 1, 31, 32, 33 and 700 positions of one token, tokens
+    outside the vocabulary (no row), the rest drawn.  dwte = the head's part +
+    the run's rows, dwpe = the sum over the batch: float32 sums of fewer than
+    720 terms in any order, each within 720 * 2^-24 (1.01 for higher orders)
+    of the exact sum times the sum of absolute values."""
+    cfg = S.GPTConfig(n_layer=1, d_model=32, n_head=1, d_ff=64, seq=seq, batch=batch, vocab=400)
     params, tokens, peers, m = gpt_setup(cfg)
     hp, _ = gpt_hp(cfg)
     N, d, V, T = cfg.batch * cfg.seq, cfg.d_model, cfg.vocab, cfg.seq
     rng = np.random.default_rng(11)
     flat = rng.integers(20, V, N).astype(np.int32)
     at = 0
-    for tok, n in ((3, 1), (4, 31), (5, 32), (6, 33), (7, 700), (-1, 5), (V, 6)):
+    for tok, n in ((3, 1), (-1, 5), (V, 6), (4, 31), (5, 32), (6, 33), (7, 700)):
         flat[at:at + n] = tok
         at += n
     tokens = np.concatenate([rng.permutation(flat).reshape(cfg.batch, T), tokens[:, -1:]], axis=1).astype(np.int32)
@@ -165,7 +167,7 @@ def test_embedding_backward_long_runs():
     ref, mag = head.copy(), np.abs(head)
     np.add.at(ref, ids[ok], dx[ok])
     np.add.at(mag, ids[ok], np.abs(dx[ok]))
-    eps = 1.01 * 701 * 2.0 ** -24
+    eps = 1.01 * 720 * 2.0 ** -24
     assert np.all(np.abs(got["wte"] - ref) <= eps * mag)
     assert np.all(np.abs(got["wpe"] - dx.sum(0)) <= eps * np.abs(dx).sum(0))
     m.close()
