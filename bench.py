@@ -670,7 +670,7 @@ def trace_overlap(path):
     `bench.py --only-step`: the compute stream is the one that runs the
     attention backward, the update stream the one that runs the update+mix.
     For the update+mix kernels, and for every kernel of the update stream
-    (dW GEMMs, the head's dW, the forward's second half, the token sort),
+    (a block's dW launch, the token sort),
     the fraction of their summed duration during which at least one
     compute-stream kernel was running, over every step in the trace
     (warm-up and timed steps are the same step)."""
@@ -928,8 +928,8 @@ def main():
         "update_mix_all_units_ms": round(um_all["round_ms"], 4),
         "critical_path_moved_ms": round(moved, 4),
         "moved_off_compute_stream": "serialized minus two-stream step time; the update stream takes the "
-                                    "update+mix of every unit, every dW GEMM with its bias sum, the head's dW, "
-                                    "the forward's second batch half and the token sort (the concurrency of "
+                                    "update+mix of every unit, the blocks' dW launches with their bias and "
+                                    "LayerNorm gradient sums, and the token sort (the concurrency of "
                                     "the update+mix itself comes from a kernel trace: bench.py --trace-overlap)",
         "drift": drift,
         "roofline": roofline,
