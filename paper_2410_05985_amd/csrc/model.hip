@@ -519,8 +519,8 @@ layup_status gpt_backward(layup_ctx* c, int u) {
     TRY(run_gemm(c, mk(false, false, Vp, d, N, c->logits, Vp, c->xf, d, fl.g("wte"), d, EPI_F32), "head dW"));
     c->cur_dx = 0;
     HIPCHK(c, launch_layernorm_bwd(c->da, c->xL, c->meanf, c->rstdf, fl.p("lnf.g"), nullptr,
-                                   c->dx[0], c->dyA[(g.n_layer - 1) & 1], c->ln_part[g.n_layer & 1][0], fl.g("lnf.g"), fl.g("lnf.b"), N,
-                                   (int)d, s), "lnf backward");
+                                   c->dx[0], c->dyA[(g.n_layer - 1) & 1], c->ln_part[g.n_layer & 1][0],
+                                   fl.g("lnf.g"), fl.g("lnf.b"), N, (int)d, s), "lnf backward");
     return LAYUP_OK;
   }
   if (u == 0) {
@@ -664,9 +664,7 @@ layup_status mlp_backward(layup_ctx* c, int u) {
     if (!m.empty()) return fail(c, LAYUP_ERR_SHAPE, "mlp backward: " + m);
   }
   HIPCHK(c, launch_gemm_f32_backward(g2[0], g2[1], c->sc), "mlp dW + db, dX");
-  {
-    std::swap(c->mlp_dz, c->mlp_dh);
-  }
+  std::swap(c->mlp_dz, c->mlp_dh);
   return LAYUP_OK;
 }
 
