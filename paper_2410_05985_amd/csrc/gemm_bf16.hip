@@ -50,16 +50,24 @@ struct KArgs {
 // GELU, tanh form: 0.5 x (1 + tanh(u)), u = sqrt(2/pi) (x + 0.044715 x^3).
 // Since 0.5 (1 + tanh(u)) = sigmoid(2u), it is x s with s = 1 / (1 + e),
 // e = e^(-2u): one exponential and a reciprocal instead of tanh.  1 - s = e s
-// keeps its relative accuracy where s is close to 1.  e is taken as 2^(-2u
-// log2(e)) directly: reducing the argument exactly first made it an ulp more
-// accurate (against float64 on bf16 x ~ N(0, 3): GELU 3.50e-8 here and 3.49e-8
-// there, its derivative 5.32e-8 and 5.26e-8, the stored bf16 values the same)
-// and was a tenth of the epilogue-bound products (8192 x 3072 x 768: 61 -> 54
-// us with GELU, 63 -> 56 us with its backward).
+// keeps its relative accuracy where s is close to 1.
+// e is 2^t, t = x (K1 + K2 x^2): an error of t counts in e in proportion to
+// |t|, so the last product's rounding error is taken from a second fma and
+// put back as e (1 + ln2 lo).  Relative error of GELU over [-5, -2], rms:
+// 3.0e-7, against 4.2e-7 with u rounded and the argument of the exponential
+// reduced exactly (five instructions more) and 4.7e-7 with 2^(-2u log2(e)).
+// x is clamped to where it matters: 2^t stays finite, with a normal
+// reciprocal, down to x = -10 (beyond it GELU is below 2e-37) and is 0 from
+// x = 13 on.
 __device__ __forceinline__ float gelu_sig(float x, float& e) {
-  const float c = 0.7978845608028654f;  // sqrt(2/pi)
-  const float u = c * fmaf(0.044715f * x, x * x, x);
-  e = __builtin_amdgcn_exp2f(fminf(-2.8853900817779268f * u, 115.0f));  // -2 log2(e)
+  const float K1 = -2.3022081981443251f;   // -2 sqrt(2/pi) log2(e)
+  const float K2 = -0.10294323958002350f;  // 0.044715 K1
+  const float xc = __builtin_amdgcn_fmed3f(x, -10.0f, 13.0f);
+  const float k = fmaf(K2, xc * xc, K1);
+  const float t = xc * k;
+  const float lo = fmaf(xc, k, -t);
+  const float p = __builtin_amdgcn_exp2f(t);
+  e = fmaf(p, lo * 0.69314718055994531f, p);
   return __builtin_amdgcn_rcpf(1.0f + e);
 }
 
@@ -1142,4 +1150,19 @@ hipError_t launch_gemm_bf16(const Gemm& g, hipStream_t s) {
   return launch_gemm_bf16_cfg(g, p.cfg, p.splits, s);
 }
 
+namespace {
+__global__ __launch_bounds__(256) void gelu_test_kernel(const float* x, float* y, float* dy, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  y[i] = gelu_tanh_f(x[i]);
+  dy[i] = gelu_tanh_grad_f(x[i]);
+}
+}  // namespace
+
 }  // namespace layup
+
+extern "C" int layup_test_gelu(const float* x, float* y, float* dy, int64_t n, void* stream) {
+  if (!x || !y || !dy || n < 1 || n > (1ll << 31)) return LAYUP_ERR_INVALID_ARG;
+  layup::gelu_test_kernel<<<(unsigned)cdiv(n, 256), 256, 0, (hipStream_t)stream>>>(x, y, dy, n);
+  return hipGetLastError() == hipSuccess ? LAYUP_OK : LAYUP_ERR_HIP;
+}

@@ -264,3 +264,11 @@ hipError_t launch_ce_f32(const float* logits, const int32_t* labels, int rows, i
                          float* dlogits, float* loss_rows, float* loss_out, hipStream_t s);
 
 }  // namespace layup
+
+// ------------------------------------------------------------ test entries
+// Not part of the public API: they reach parts of the kernels that no public
+// call exposes by itself.  Each returns a layup_status.
+extern "C" {
+// GELU and its derivative of x, float32, as the GEMM epilogues compute them.
+int layup_test_gelu(const float* x, float* y, float* dy, int64_t n, void* stream);
+}

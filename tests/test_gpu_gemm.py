@@ -4,6 +4,9 @@ dW = dY^T X products of the linear layers' backward (Algorithm 1, backward
 pass at one layer), the forward product and the batched attention products.
 Tolerance: rel 2e-2 for bf16-input GEMMs (float32 output is additionally held
 to 1e-4 normwise)."""
+import ctypes
+import math
+
 import numpy as np
 import pytest
 
@@ -296,3 +299,52 @@ def test_gemm_tiles_and_short_k(layout, M, N, K):
     assert torch.all((C.double() - a @ b).abs() <= 2 * (K + 8) * 2.0 ** -24 * (a.abs() @ b.abs()))
     if rs is not None:
         assert torch.all((rs.double() - a.sum(1)).abs() <= 2 * (K + 8) * 2.0 ** -24 * a.abs().sum(1))
+
+
+def _gelu64(x):
+    """GELU (tanh form) of float64 x: value, derivative, and s, 2u, x s' of them."""
+    c = math.sqrt(2.0 / math.pi)
+    u2 = 2.0 * c * (x + 0.044715 * x ** 3)
+    e = torch.exp(-u2)
+    s = 1.0 / (1.0 + e)
+    t = x * s * (e * s) * 2.0 * c * (1.0 + 3.0 * 0.044715 * x * x)
+    return x * s, s + t, s, u2, t
+
+
+def _gelu_epilogue(x, y, dy):
+    f = LU.lib().layup_test_gelu
+    f.argtypes = [ctypes.c_void_p] * 3 + [ctypes.c_int64, ctypes.c_void_p]
+    assert f(x.data_ptr(), y.data_ptr(), dy.data_ptr(), x.numel(), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("lo,hi", [(-9.9, -5.0), (-5.0, -1.0), (-1.0, 1.0), (1.0, 10.0)])
+def test_gelu_epilogue_arithmetic(lo, hi):
+    """The GELU of the epilogues in float32, before the bfloat16 store, at four
+    million points a range.  With eps = 2^-24: the exponent t = -2u log2(e)
+    carries at most 2 eps (half an ulp each of x^2, weighted by its share, and
+    of K1 + K2 x^2, and their constants), which costs e at most 2 |2u| eps, of
+    which 1 - s reaches s; the exponential, reciprocal (an ulp each), sums and
+    products add at most 6 eps.  The derivative s + t (t = x s' has s (1 - s))
+    adds the same once more to each term."""
+    x = torch.linspace(lo, hi, 4_000_001, dtype=torch.float32, device=DEV)
+    y, dy = torch.empty_like(x), torch.empty_like(x)
+    _gelu_epilogue(x, y, dy)
+    ref, dref, s, u2, t = _gelu64(x.double())
+    eps = 2.0 ** -24
+    rel_s = 2 * u2.abs() * (1 - s) + 6
+    assert torch.all((y.double() - ref).abs() <= eps * rel_s * ref.abs())
+    rel_t = 2 * u2.abs() * (1 - 2 * s).abs() + 12
+    assert torch.all((dy.double() - dref).abs() <= eps * (rel_s * s + rel_t * t.abs()))
+
+
+def test_gelu_epilogue_extremes():
+    """Far from zero: GELU is x (and its derivative 1) to the right; to the
+    left s <= 2^-125, so it is below 2e-37 |x| in magnitude and its derivative
+    below 2e-37 |x| (1 + x^2); NaN stays NaN."""
+    x = torch.tensor([12.9, 13.0, 100.0, 1e12, -10.0, -13.0, -1e4, 0.0, float("nan")], device=DEV)
+    y, dy = torch.empty_like(x), torch.empty_like(x)
+    _gelu_epilogue(x, y, dy)
+    assert torch.equal(y[:4], x[:4]) and torch.equal(dy[:4], torch.ones_like(x[:4]))
+    assert torch.all(y[4:7].abs() <= 2e-37 * x[4:7].abs()) and torch.all(dy[4:7].abs() <= 2e-37 * x[4:7].abs() * (1 + x[4:7] ** 2))
+    assert y[7] == 0 and dy[7] == 0.5 and torch.isnan(y[8]) and torch.isnan(dy[8])
