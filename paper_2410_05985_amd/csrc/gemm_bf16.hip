@@ -45,6 +45,7 @@ struct KArgs {
   int64_t k_per_split;
   UpdArgs upd;             // EPI_UPDATE
   float* rowsum;           // row sums of an m-major A (split-K: partials after the C partials)
+  int64_t run;             // FL: the longest run of products of one accumulator
 };
 
 // GELU, tanh form: 0.5 x (1 + tanh(u)), u = sqrt(2/pi) (x + 0.044715 x^3).
@@ -402,7 +403,8 @@ __device__ __forceinline__ void barrier_only() {
 // 32x32 MFMA tiles.  STAGES LDS stages of the BM x BKV and BN x BKV operand
 // tiles.  This is the work of one workgroup: item `lid` of P's flat list of
 // (batch or split, tile) work items.
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool AK, bool BKM, int EPI, bool SPLIT, int BKV>
+// FL: the accumulators take at most P.run products in a row.
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool AK, bool BKM, int EPI, bool SPLIT, int BKV, bool FL>
 __device__ __forceinline__ void gemm_item(const KArgs& P, int lid) {
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
@@ -463,6 +465,41 @@ __device__ __forceinline__ void gemm_item(const KArgs& P, int lid) {
   float rsum[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) rsum[i] = 0.f;
+
+  // FL: after every P.run products the accumulators (and row sums) are added
+  // into a second set and start again from zero.  A float32 sum of K products
+  // has an error that grows with the square root of the run: over K = 8192 it
+  // is 5.7e-7 of the result in one run, 2.7e-7 in runs of 2048 (or as the sum
+  // of four split-K partials) and 1.5e-7 in runs of 512.  Runs of 512 cost 1
+  // to 3 % of the K loop.  The second set fits the register file up to 64
+  // accumulators a thread; row sums keep theirs in LDS, each lane its own.
+  static_assert(!FL || TM * TN <= 4, "registers for two sets of accumulators");
+  f32x16 tot[FL ? TM : 1][FL ? TN : 1];
+  __shared__ float rs_tot[FL && !AK ? WGM * TM * 64 : 1];
+  if constexpr (FL) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) tot[i][j][r] = 0.f;
+      if (rs_on) rs_tot[(wm * TM + i) * 64 + lane] = 0.f;
+    }
+  }
+  auto flush = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          tot[i][j][r] += acc[i][j][r];
+          acc[i][j][r] = 0.f;
+        }
+      if (rs_on) rs_tot[(wm * TM + i) * 64 + lane] += rsum[i];
+      rsum[i] = 0.f;
+    }
+  };
 
   // per-lane fragment offsets inside a stage (B after A)
   constexpr int NA = AK ? KS : TM, NB = BKM ? KS : TN;
@@ -611,15 +648,33 @@ __device__ __forceinline__ void gemm_item(const KArgs& P, int lid) {
   };
   for (int t = 0; t < S - 1; ++t) issue_step(t, t);
   int kt = 0, slot = 0;
+  const int run = FL ? (int)min(P.run / BKV, (int64_t)1 << 30) : 0;  // K steps
+  int left = run;
   for (; kt + S - 1 < n_full; ++kt) {
     k_step(IntC<1>{}, kt, slot);
     slot = slot + 1 == S ? 0 : slot + 1;
+    if constexpr (FL) {
+      if (--left == 0) {
+        flush();
+        left = run;
+      }
+    }
   }
   for (; kt < nk; ++kt) {
     k_step(IntC<0>{}, kt, slot);
     slot = slot + 1 == S ? 0 : slot + 1;
   }
   multiply(IntC<1>{}, IntC<0>{}, 0);
+  if constexpr (FL) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] += tot[i][j][r];
+      if (rs_on) rsum[i] += rs_tot[(wm * TM + i) * 64 + lane];
+    }
+  }
 
   // ---- epilogue.  32x32 accumulator layout: lane l, register r holds
   // row (r/4)*8 + (l/32)*4 + r%4, column l%32 of the 32x32 block.  Each block
@@ -695,12 +750,13 @@ __device__ __forceinline__ int work_item(int n) {
 }
 
 // OCC: workgroups per CU.
-template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, bool AK, bool BKM, int EPI, bool SPLIT, int BKV>
-__global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_kernel(const KArgs P) {
+template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, bool AK, bool BKM, int EPI, bool SPLIT, int BKV,
+          bool FL>
+__global__ __launch_bounds__(64 * WGM * WGN, FL ? OCC * WGM * WGN / 4 : OCC) void gemm_bf16_kernel(const KArgs P) {
   const int n = P.tiles_m * P.tiles_n * (SPLIT ? P.splits : P.nz);
   const int lid = work_item(n);
   if (lid >= n) return;
-  gemm_item<BM, BN, WGM, WGN, STAGES, AK, BKM, EPI, SPLIT, BKV>(P, lid);
+  gemm_item<BM, BN, WGM, WGN, STAGES, AK, BKM, EPI, SPLIT, BKV, FL>(P, lid);
 }
 
 // Several products dW = dY^T X in one launch (GemmGroup): the work items of
@@ -716,7 +772,7 @@ struct GroupArgs {
 };
 
 template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool SPLIT, int BKV>
-__global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_group_kernel(const GroupArgs G) {
+__global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void gemm_bf16_group_kernel(const GroupArgs G) {
   const int n = G.first[G.n], ng = (n + 7) / 8 * 8;
   if ((int)blockIdx.x >= ng) {
     // the LayerNorm sums follow the products: they run on the CUs the last round leaves free
@@ -732,7 +788,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_group_kernel(co
   if (lid >= n) return;
   int i = 0;
   while (i + 1 < G.n && lid >= G.first[i + 1]) ++i;
-  gemm_item<BM, BN, WGM, WGN, STAGES, false, false, EPI, SPLIT, BKV>(G.p[i], lid - G.first[i]);
+  gemm_item<BM, BN, WGM, WGN, STAGES, false, false, EPI, SPLIT, BKV, BM * BN <= 256 * 128>(G.p[i], lid - G.first[i]);
 }
 
 // Sum over the splits, in split order, of the partials of four consecutive
@@ -838,7 +894,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_group_kernel(const GroupArg
   splitk_reduce_item<EPI>(G.p[i], (int64_t)(b - G.rfirst[i]) * 256 + threadIdx.x);
 }
 
-template <int BM, int BN, int WGM, int WGN, int STG, int OCC, bool AK, bool BKM, int EPI, int BKV>
+template <int BM, int BN, int WGM, int WGN, int STG, int OCC, bool AK, bool BKM, int EPI, int BKV, bool FL = false>
 hipError_t launch_tiles(const KArgs& P, int batch, hipStream_t s) {
   const int64_t n_log = (int64_t)P.tiles_m * P.tiles_n * (P.splits > 1 ? P.splits : batch);
   if (n_log >= (1ll << 31) - 8) return hipErrorInvalidValue;
@@ -846,7 +902,7 @@ hipError_t launch_tiles(const KArgs& P, int batch, hipStream_t s) {
   constexpr int NT = 64 * WGM * WGN;
   if constexpr (EPI == EPI_F32 || EPI == EPI_UPDATE) {
     if (P.splits > 1) {
-      gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, true, BKV><<<grid, NT, 0, s>>>(P);
+      gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, true, BKV, FL><<<grid, NT, 0, s>>>(P);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
       const int64_t groups = P.M * cdiv(P.N, 4);
@@ -855,18 +911,35 @@ hipError_t launch_tiles(const KArgs& P, int batch, hipStream_t s) {
       return hipGetLastError();
     }
   }
-  gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, false, BKV><<<grid, NT, 0, s>>>(P);
+  gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, false, BKV, FL><<<grid, NT, 0, s>>>(P);
   return hipGetLastError();
+}
+
+// Which products can be summed in short runs (FL): float32 results, tiles
+// whose two sets of accumulators fit the registers.  (128 x 128, two a CU, has
+// 128 registers a thread: enough for the addresses of m-major operands only.)
+constexpr int64_t ANY_RUN = 1ll << 62;
+constexpr bool can_flush(int bm, int bn, bool a_kmajor) {
+  return bm * bn <= 256 * 128 && !(a_kmajor && bm == 128 && bn == 128);
+}
+
+template <int BM, int BN, int WGM, int WGN, int STG, int OCC, int BKV, int EPI, bool AK, bool BKM>
+hipError_t dispatch_flush(const Gemm& g, const KArgs& P, hipStream_t s) {
+  const bool flush = P.run < (P.splits > 1 ? P.k_per_split : P.K);
+  if constexpr (EPI == EPI_F32 && can_flush(BM, BN, AK))
+    if (flush) return launch_tiles<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, BKV, true>(P, g.batch, s);
+  if (flush) return hipErrorInvalidValue;
+  return launch_tiles<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, BKV>(P, g.batch, s);
 }
 
 template <int BM, int BN, int WGM, int WGN, int STG, int OCC, int BKV, int EPI>
 hipError_t dispatch_layout(const Gemm& g, const KArgs& P, hipStream_t s) {
   if (g.a_kmajor && g.b_kmajor)
-    return launch_tiles<BM, BN, WGM, WGN, STG, OCC, true, true, EPI, BKV>(P, g.batch, s);
+    return dispatch_flush<BM, BN, WGM, WGN, STG, OCC, BKV, EPI, true, true>(g, P, s);
   if (g.a_kmajor && !g.b_kmajor)
-    return launch_tiles<BM, BN, WGM, WGN, STG, OCC, true, false, EPI, BKV>(P, g.batch, s);
+    return dispatch_flush<BM, BN, WGM, WGN, STG, OCC, BKV, EPI, true, false>(g, P, s);
   if (!g.a_kmajor && !g.b_kmajor)
-    return launch_tiles<BM, BN, WGM, WGN, STG, OCC, false, false, EPI, BKV>(P, g.batch, s);
+    return dispatch_flush<BM, BN, WGM, WGN, STG, OCC, BKV, EPI, false, false>(g, P, s);
   return hipErrorInvalidValue;  // m-major A with k-major B: no caller needs it
 }
 
@@ -910,6 +983,7 @@ KArgs make_args(const Gemm& g) {
   P.nz = g.batch;
   P.upd = g.upd;
   P.rowsum = g.rowsum;
+  P.run = ANY_RUN;
   return P;
 }
 
@@ -995,6 +1069,27 @@ hipError_t launch_group(const GroupArgs& G, int epi, bool split, hipStream_t s) 
 }
 }  // namespace
 
+// The longest run of products that one accumulator of a float32 result may
+// take.  Splitting K to fill the chip (at least 512 k each, at most 8 splits,
+// two 128 x 128 tiles a CU) also shortens the runs, and with them the rounding
+// error of a gradient; a plan that fills the chip without the split, by a
+// smaller tile or by grouping products, keeps the sums as accurate by the
+// FL form.  No limit where K would not be split: enough tiles, a
+// short K, forward products, too little workspace.
+static int64_t run_limit(const Gemm& g) {
+  auto tiles = [&](int t) { return cdiv(g.M, t) * cdiv(g.N, t); };
+  if ((g.epi != EPI_F32 && g.epi != EPI_UPDATE) || g.batch != 1 || !g.splitk_ws || g.K < 1536 || g.M > 65535 ||
+      g.N <= 64 || (g.M >= 2048 && g.N >= 2048 && tiles(256) >= 256))
+    return ANY_RUN;
+  int64_t splits = 8;
+  if (!g.a_kmajor || g.K < 16384) {
+    if (g.b_kmajor || tiles(128) > 256) return ANY_RUN;
+    splits = std::min<int64_t>(512 / tiles(128), std::min<int64_t>(8, g.K / 512));
+  }
+  splits = std::min<int64_t>(splits, g.splitk_ws_bytes / ((g.M * g.N + (g.rowsum ? g.M : 0)) * 4));
+  return splits < 2 ? ANY_RUN : cdiv(cdiv(g.K, splits), 32) * 32;
+}
+
 // The products share K, the epilogue (float32 or the weight update) and the
 // split-K workspace, which splits > 1 needs room in for all of them.
 hipError_t launch_gemm_bf16_group_cfg(const Gemm* g, int n, const LnSum* ln, int n_ln, int cfg, int splits,
@@ -1030,6 +1125,7 @@ hipError_t launch_gemm_bf16_group_cfg(const Gemm* g, int n, const LnSum* ln, int
     P = make_args(g[i]);
     P.tiles_m = (int)cdiv(P.M, BM);
     P.tiles_n = (int)cdiv(P.N, BN);
+    P.run = run_limit(g[i]);
     G.first[i] = (int)items;
     G.rfirst[i] = (int)rblocks;
     items += (int64_t)P.tiles_m * P.tiles_n * splits;
@@ -1052,7 +1148,7 @@ hipError_t launch_gemm_bf16_group_cfg(const Gemm* g, int n, const LnSum* ln, int
   }
 }
 
-hipError_t launch_gemm_bf16_cfg(const Gemm& g, int cfg, int splits, hipStream_t s) {
+hipError_t launch_gemm_bf16_cfg(const Gemm& g, int cfg, int splits, int64_t run, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return hipSuccess;
   if (cfg < 0 || cfg >= kNumCfg) return hipErrorInvalidValue;
   KArgs P = make_args(g);
@@ -1068,6 +1164,7 @@ hipError_t launch_gemm_bf16_cfg(const Gemm& g, int cfg, int splits, hipStream_t 
       P.partial = g.splitk_ws;
     }
   }
+  P.run = run;
   switch (cfg) {
     case T256x256: return dispatch_epi<256, 256, 2, 4, 2, 1, 64>(g, P, s);
     case T256x192: return dispatch_epi<256, 192, 4, 2, 2, 1, 64>(g, P, s);
@@ -1103,23 +1200,33 @@ static float est_items(const TileCfg& t, int64_t items, float steps, float bytes
 // Tile and split of K for a product or a group of products with the same K:
 // the smallest estimate over the configurations and splits, the split's
 // partial sums written and read back at 4.5 TB/s by a second launch (8 us).
-// A split leaves at least 512 k each, at most 8 of them.
+// A split leaves at least 512 k each, at most 8 of them.  A tile that would
+// exceed the run limit takes its FL form (1 % more a step) or is left out.
+// beside: the launch shares the chip with another stream's kernels, and what it
+// takes from them counts besides its own time: tiles of several workgroups a CU
+// leave them no CU, a split adds work.  Both count a tenth more: the GPT-2-small
+// step takes 11.65 ms with 128 x 128 and 11.42 with 256 x 128, four blocks of
+// GPT-2-medium's width 7.85 ms with 128 x 128, 7.87 with 256 x 128 and K split
+// in two, and 7.73 with 256 x 128.
 struct Plan {
   int cfg = T128x128, splits = 1;
+  int64_t run = ANY_RUN;
+  float us = 3.4e38f;
 };
-static Plan choose(const Gemm* g, int n, bool group) {
+static Plan choose(const Gemm* g, int n, bool group, bool beside) {
   const bool splittable = g[0].batch == 1 && (g[0].epi == EPI_F32 || g[0].epi == EPI_UPDATE) && g[0].splitk_ws;
   double outputs = 0.0;
   size_t per_split = 0;
+  int64_t limit = ANY_RUN;
   for (int i = 0; i < n; ++i) {
     outputs += (double)g[i].M * g[i].N;
     per_split += ((size_t)g[i].M * g[i].N + (g[i].rowsum ? g[i].M : 0)) * 4 + 256;
+    limit = std::min(limit, run_limit(g[i]));
   }
   float bytes = g[0].epi == EPI_F32 ? 4.f : g[0].epi == EPI_BF16 ? 2.f : g[0].epi == EPI_UPDATE ? 30.f : 4.f;
   if (g[0].epi == EPI_F32 && g[0].aux) bytes += 4.f;
   const int64_t max_split = splittable ? std::min<int64_t>(8, g[0].K / 512) : 1;
   Plan best;
-  float best_us = 3.4e38f;
   for (int c = 0; c < kNumCfg; ++c) {
     if (group && c != T256x256 && c != T256x128 && c != T128x128) continue;
     const TileCfg& t = kCfgs[c];
@@ -1127,27 +1234,28 @@ static Plan choose(const Gemm* g, int n, bool group) {
     for (int i = 0; i < n; ++i) tiles += cdiv(g[i].M, t.bm) * cdiv(g[i].N, t.bn) * g[i].batch;
     for (int sp = 1; sp <= std::max<int64_t>(1, max_split); ++sp) {
       if (sp > 1 && (sp * per_split > g[0].splitk_ws_bytes || g[0].M > 65535)) break;
-      const float steps = (float)cdiv(cdiv(g[0].K, sp), 64) * (g[0].a_kmajor ? 1.0f : t.dw);
+      const int64_t run = sp > 1 ? cdiv(cdiv(g[0].K, sp), 32) * 32 : g[0].K;
+      const bool flush = run > limit;
+      if (flush && !can_flush(t.bm, t.bn, g[0].a_kmajor)) continue;
+      const float steps = (float)cdiv(cdiv(g[0].K, sp), 64) * (g[0].a_kmajor ? 1.0f : t.dw) * (flush ? 1.01f : 1.0f);
       float us = est_items(t, tiles * sp, steps, sp > 1 ? 4.f : bytes);
       if (sp > 1) us += 8.f + (float)(outputs * (4.0 * sp + bytes) / 4.5e6);
-      if (us < best_us) {
-        best_us = us;
-        best = Plan{c, sp};
-      }
+      if (beside && (t.occ > 1 || sp > 1)) us *= 1.1f;
+      if (us < best.us) best = Plan{c, sp, limit, us};
     }
   }
   return best;
 }
 
-hipError_t launch_gemm_bf16_group(const Gemm* g, int n, const LnSum* ln, int n_ln, hipStream_t s) {
-  const Plan p = choose(g, n, true);
+hipError_t launch_gemm_bf16_group(const Gemm* g, int n, const LnSum* ln, int n_ln, bool beside, hipStream_t s) {
+  const Plan p = choose(g, n, true, beside);
   return launch_gemm_bf16_group_cfg(g, n, ln, n_ln, p.cfg, p.splits, s);
 }
 
 hipError_t launch_gemm_bf16(const Gemm& g, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return hipSuccess;
-  const Plan p = choose(&g, 1, false);
-  return launch_gemm_bf16_cfg(g, p.cfg, p.splits, s);
+  const Plan p = choose(&g, 1, false, false);
+  return launch_gemm_bf16_cfg(g, p.cfg, p.splits, p.run, s);
 }
 
 namespace {

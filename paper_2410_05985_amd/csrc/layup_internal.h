@@ -208,9 +208,13 @@ __device__ __forceinline__ void ln_sum_item(const LnSum& L, int team, int tid, f
 
 // Up to four products dW = dY^T X of the same K and epilogue (float32 or the
 // weight update; batch 1) in one launch; the split-K workspace is g[0]'s.
-// Up to two LayerNorm gradient sums (of one width) ride along.
+// Up to two LayerNorm gradient sums (of one width) ride along.  beside: other
+// kernels run on another stream meanwhile.
 constexpr int GEMM_GROUP_MAX = 4;
-hipError_t launch_gemm_bf16_group(const Gemm* g, int n, const LnSum* ln, int n_ln, hipStream_t stream);
+hipError_t launch_gemm_bf16_cfg(const Gemm& g, int cfg, int splits, int64_t run, hipStream_t stream);
+hipError_t launch_gemm_bf16_group_cfg(const Gemm* g, int n, const LnSum* ln, int n_ln, int cfg, int splits,
+                                      hipStream_t stream);
+hipError_t launch_gemm_bf16_group(const Gemm* g, int n, const LnSum* ln, int n_ln, bool beside, hipStream_t stream);
 hipError_t launch_gemm_f32(const Gemm& g, hipStream_t stream);
 // dW (m-major operands) and dX (k-major A) of one linear layer, in one launch where both are small
 hipError_t launch_gemm_f32_backward(const Gemm& dw, const Gemm& dx, hipStream_t stream);
@@ -271,4 +275,10 @@ hipError_t launch_ce_f32(const float* logits, const int32_t* labels, int rows, i
 extern "C" {
 // GELU and its derivative of x, float32, as the GEMM epilogues compute them.
 int layup_test_gelu(const float* x, float* y, float* dy, int64_t n, void* stream);
+// n products with the tile configuration (TileId) and split of K given: as one
+// group launch (group != 0, 2: beside other kernels; dW = dY^T X only), or a single product, summed in
+// runs of at most `run` products (>= 64).  cfg < 0: the plan the library chooses.  upd, when
+// given, holds the tensors of the update epilogue, one per product.
+int layup_test_gemm_tile(const layup_gemm_desc* d, int32_t n, int32_t group, int32_t cfg, int32_t splits,
+                         int64_t run, const layup_tensor* upd, const layup_hparams* hp, float alpha, void* stream);
 }

@@ -418,7 +418,7 @@ layup_status run_gemm_group(layup_ctx* c, Gemm* g, int n, const LnSum* ln, int n
     if (!m.empty()) return fail(c, LAYUP_ERR_SHAPE, std::string(what) + ": " + m);
   }
   if (c->gemm_timing) TRY(timing_start(c, s));
-  HIPCHK(c, launch_gemm_bf16_group(g, n, ln, n_ln, s), what);
+  HIPCHK(c, launch_gemm_bf16_group(g, n, ln, n_ln, s != c->sc, s), what);
   if (c->gemm_timing) TRY(timing_stop(c, g, n, s));
   return LAYUP_OK;
 }
@@ -542,7 +542,7 @@ layup_status gpt_backward(layup_ctx* c, int u) {
   // one launch, on the update stream or here (dw_side).  In the fused
   // schedule they update the weights in place, after the chain has read them.
   // One launch of all four needs no split-K to fill the chip: 4 x 45 us and
-  // four sums of 8 us became 144 us per GPT-2-small block.
+  // four sums of 8 us became 155 us per GPT-2-small block (alone on the chip).
   // MLP output projection: dY = dyA (written by the LayerNorm backward that produced dxo)
   Gemm dg = mk(true, false, N, F, d, dyA, d, fl.w16(p + "mproj.w"), F, df16, F, EPI_DGELU);
   dg.aux = A.f;
@@ -1324,9 +1324,9 @@ layup_status layup_activation(layup_ctx* ctx, int32_t which, int32_t layer, cons
   return LAYUP_OK;
 }
 
-static layup_status gemm_abi(const layup_gemm_desc* d, void* stream, bool f32) {
+// The checked product of a descriptor.
+static layup_status gemm_of(const layup_gemm_desc* d, bool f32, Gemm& g) {
   if (!d) return fail(nullptr, LAYUP_ERR_INVALID_ARG, "null descriptor");
-  Gemm g;
   g.a_kmajor = d->a_kmajor != 0;
   g.b_kmajor = d->b_kmajor != 0;
   g.M = d->M;
@@ -1358,12 +1358,46 @@ static layup_status gemm_abi(const layup_gemm_desc* d, void* stream, bool f32) {
   std::string m = gemm_check(g, f32);
   if (!m.empty()) return fail(nullptr, m.find("aligned") != std::string::npos || m.find("multiple") != std::string::npos
                                            ? LAYUP_ERR_ALIGN : LAYUP_ERR_SHAPE, m);
-  hipError_t e = f32 ? launch_gemm_f32(g, (hipStream_t)stream) : launch_gemm_bf16(g, (hipStream_t)stream);
+  return LAYUP_OK;
+}
+
+static layup_status gemm_abi(const layup_gemm_desc* d, void* stream, bool f32) {
+  Gemm g;
+  TRY(gemm_of(d, f32, g));
+  const hipError_t e = f32 ? launch_gemm_f32(g, (hipStream_t)stream) : launch_gemm_bf16(g, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(nullptr, e, "gemm");
   return LAYUP_OK;
 }
 
 layup_status layup_gemm_bf16(const layup_gemm_desc* d, void* stream) { return gemm_abi(d, stream, false); }
 layup_status layup_gemm_f32(const layup_gemm_desc* d, void* stream) { return gemm_abi(d, stream, true); }
+
+int layup_test_gemm_tile(const layup_gemm_desc* d, int32_t n, int32_t group, int32_t cfg, int32_t splits,
+                         int64_t run, const layup_tensor* upd, const layup_hparams* hp, float alpha, void* stream) {
+  if (!d || n < 1 || n > GEMM_GROUP_MAX || (!group && n != 1) || splits < 1 || run < 64)
+    return fail(nullptr, LAYUP_ERR_INVALID_ARG, "bad product list");
+  Gemm g[GEMM_GROUP_MAX];
+  for (int i = 0; i < n; ++i) {
+    TRY(gemm_of(&d[i], false, g[i]));
+    if (!upd) continue;
+    const std::string m = check_hp(hp);
+    if (!m.empty()) return fail(nullptr, LAYUP_ERR_INVALID_ARG, m);
+    g[i].epi = EPI_UPDATE;
+    g[i].upd = make_upd_args(*hp, alpha, upd[i].decay != 0);
+    g[i].upd.p = upd[i].param;
+    g[i].upd.m = upd[i].state0;
+    g[i].upd.v = upd[i].state1;
+    g[i].upd.q = upd[i].peer;
+    g[i].upd.p16 = (bf16_t*)upd[i].param_bf16;
+    const std::string m2 = gemm_check(g[i], false);
+    if (!m2.empty()) return fail(nullptr, LAYUP_ERR_SHAPE, m2);
+  }
+  const hipStream_t s = (hipStream_t)stream;
+  hipError_t e;
+  if (group) e = cfg < 0 ? launch_gemm_bf16_group(g, n, nullptr, 0, group > 1, s)
+                         : launch_gemm_bf16_group_cfg(g, n, nullptr, 0, cfg, splits, s);
+  else e = cfg < 0 ? launch_gemm_bf16(g[0], s) : launch_gemm_bf16_cfg(g[0], cfg, splits, run, s);
+  return e == hipSuccess ? LAYUP_OK : hip_fail(nullptr, e, "gemm");
+}
 
 }  // extern "C"

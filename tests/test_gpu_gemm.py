@@ -348,3 +348,74 @@ def test_gelu_epilogue_extremes():
     assert torch.equal(y[:4], x[:4]) and torch.equal(dy[:4], torch.ones_like(x[:4]))
     assert torch.all(y[4:7].abs() <= 2e-37 * x[4:7].abs()) and torch.all(dy[4:7].abs() <= 2e-37 * x[4:7].abs() * (1 + x[4:7] ** 2))
     assert y[7] == 0 and dy[7] == 0.5 and torch.isnan(y[8]) and torch.isnan(dy[8])
+
+
+def _tile(descs, group=0, cfg=-1, splits=1, run=1 << 62, upd=None, hp=None, alpha=0.5):
+    """Products through the test entry: tile configuration and split given, or (cfg < 0) chosen by the library."""
+    f = LU.lib().layup_test_gemm_tile
+    f.argtypes = [ctypes.c_void_p] + [ctypes.c_int32] * 4 + [ctypes.c_int64] + \
+        [ctypes.c_void_p] * 2 + [ctypes.c_float, ctypes.c_void_p]
+    arr = (LU.layup_gemm_desc * len(descs))(*descs)
+    ups = (LU.layup_tensor * len(descs))(*upd) if upd else None
+    st = f(ctypes.addressof(arr), len(descs), group, cfg, splits, run,
+           ctypes.addressof(ups) if upd else None, ctypes.addressof(hp) if hp else None, alpha,
+           torch.cuda.current_stream().cuda_stream)
+    assert st == 0, LU.lib().layup_global_error()
+    torch.cuda.synchronize()
+
+
+class _Prod:
+    """Operands (bf16 of unit normals), outputs and float64 reference of one product."""
+
+    def __init__(self, layout, M, N, K, ws=None, seed=0):
+        ak, bk = {"kk": (True, True), "kn": (True, False), "mn": (False, False)}[layout]
+        g = torch.Generator(device=DEV).manual_seed(seed + M + 3 * N + 5 * K)
+        A = torch.randn((M, K) if ak else (K, M), device=DEV, generator=g).to(torch.bfloat16)
+        B = torch.randn((N, K) if bk else (K, N), device=DEV, generator=g).to(torch.bfloat16)
+        self.A, self.B, self.C = A, B, torch.full((M, N), float("nan"), device=DEV)
+        self.rs = None if ak else torch.full((M,), float("nan"), device=DEV)
+        self.desc = LU.gemm_desc(A, B, self.C, M, N, K, K if ak else M, K if bk else N, N, ak, bk, True,
+                                 workspace=ws, workspace_bytes=ws.numel() if ws is not None else 0, a_rowsum=self.rs)
+        self.a, self.b = (A if ak else A.t().contiguous()), (B.t().contiguous() if bk else B)
+
+    def ref(self):
+        return self.a.double() @ self.b.double()
+
+    def rel(self):
+        ref = self.ref()
+        return float((self.C.double() - ref).norm() / ref.norm())
+
+
+# the error of a float32 sum of K products in one run of the matrix instruction: 16 of them take two roundings, each
+# off by 0.41 x 2^-24 of the partial sum (rms over a binade), whose square grows linearly: sqrt(run / 16) in all; a
+# fifth more for the instruction's own additions and the sum of the runs
+def _run_error(run):
+    return 1.2 * 0.41 * (run / 16) ** 0.5 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("d,ff,tokens,runs", [
+    (768, 3072, 8192, (2048, 1024, 2752, 2752)),     # splits of 4, 8, 3 and 3
+    (1024, 4096, 8192, (4096, 1024, 4096, 4096)),    # 2, 8, 2 and 2
+    (2048, 8192, 8192, (8192, 4096, 8192, 8192)),    # enough tiles for whole sums but for the attention projection
+])
+def test_block_weight_gradients_are_summed_in_short_runs(d, ff, tokens, runs):
+    """The four dW products of a block as one group: none is summed in longer
+    runs than where K is split to fill the chip with 128 x 128 tiles."""
+    ws = torch.empty(128 << 20, dtype=torch.uint8, device=DEV)
+    ps = [_Prod("mn", m, n, tokens, ws) for m, n in ((3 * d, d), (d, d), (ff, d), (d, ff))]
+    for beside in (False, True):
+        _tile([p.desc for p in ps], group=2 if beside else 1)
+        for p, run in zip(ps, runs):
+            assert p.rel() <= _run_error(run), (p.C.shape, p.rel())
+
+
+@pytest.mark.parametrize("layout,M,N,K,run", [("kn", 8192, 768, 50304, 6304), ("kn", 8192, 1024, 50304, 6304),
+                                              ("kn", 1368, 832, 3304, 576), ("kn", 2048, 2048, 8192, 4096),
+                                              ("mn", 768, 768, 8192, 1024)])
+def test_long_products_are_summed_in_short_runs(layout, M, N, K, run):
+    """The same for single products, through the public call."""
+    ws = torch.empty(256 << 20, dtype=torch.uint8, device=DEV)
+    p = _Prod(layout, M, N, K, ws)
+    LU.layup_gemm_bf16(p.desc, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert p.rel() <= _run_error(run), p.rel()
