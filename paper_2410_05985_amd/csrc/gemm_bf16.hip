@@ -611,7 +611,10 @@ __device__ __forceinline__ void gemm_item(const KArgs& P, int lid) {
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  // MAIN: step kt + S - 1 is a whole one (no branch inside)
+  // MAIN: step kt + S - 1 is a whole one.  The only branch while reads are in
+  // flight is the row sums' (multiply): the compiler could move a register of
+  // one there, and the tests follow the built code's paths to see that no
+  // instruction touches one before its wait.
   auto k_step = [&](auto MAIN, int kt, int slot) {
     constexpr bool main = decltype(MAIN)::value != 0;
     const int pslot = slot == 0 ? S - 1 : slot - 1;  // of steps kt - 1 and kt + S - 1
@@ -631,8 +634,8 @@ __device__ __forceinline__ void gemm_item(const KArgs& P, int lid) {
         __syncthreads();
       }
     }
+    if constexpr (!main) issue_step(kt + S - 1, pslot);  // its branches before the reads
     read_sub(IntC<0>{}, slot);
-    if constexpr (!main) issue_step(kt + S - 1, pslot);
     multiply(IntC<1>{}, IntC<main ? 1 : 0>{}, pslot);
     static_for<0, KS - 1>([&](auto KSI) {
       constexpr int ks = decltype(KSI)::value;
