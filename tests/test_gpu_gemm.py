@@ -276,6 +276,28 @@ def test_gemm_f32_tiles_and_remainders(ak, bk, M, N, K, ld):
     assert torch.all((C.cpu().double() - a @ b).abs() <= bound)
 
 
+@pytest.mark.parametrize("ak,bk", [(True, True), (True, False), (False, False), (False, True)])
+@pytest.mark.parametrize("M,N,K,ld", [(2048, 2048, 256, 0), (2052, 2044, 260, 4), (2049, 2051, 275, 1),
+                                      (2044, 2050, 300, 2), (70000, 68, 257, 0), (64, 65600, 256, 0)])
+def test_gemm_f32_large_tiles(ak, bk, M, N, K, ld):
+    """The 64 x 64 tiles of large products (at least 1024 of them, K >= 256):
+    whole and ragged, with and without the vector loads of rows and stores of
+    columns.  Bound as above."""
+    g = torch.Generator(device=DEV).manual_seed(M + 7 * N + 13 * K)
+    A = torch.randn((M, K + ld) if ak else (K, M + ld), device=DEV, generator=g)
+    B = torch.randn((N, K + ld) if bk else (K, N + ld), device=DEV, generator=g)
+    bias = torch.randn(N, device=DEV, generator=g)
+    a = (A[:, :K] if ak else A[:, :M].t()).double()
+    b = (B[:, :K].t() if bk else B[:, :N]).double()
+    C = torch.full((M + 1, N + ld), float("nan"), device=DEV)
+    LU.layup_gemm_f32(LU.gemm_desc(A, B, C, M, N, K, A.shape[1], B.shape[1], N + ld, ak, bk, True, bias=bias),
+                      torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    bound = 1.01 * (K + 2) * 2.0 ** -24 * (a.abs() @ b.abs() + bias.double().abs())
+    assert torch.all((C[:M, :N].double() - a @ b - bias.double()).abs() <= bound)
+    assert torch.all(torch.isnan(C[M])) and torch.all(torch.isnan(C[:, N:]))
+
+
 @pytest.mark.parametrize("layout", ["kk", "kn", "mn"])
 @pytest.mark.parametrize("M,N", [(8192, 768), (8192, 3072), (4104, 4096), (2048, 8192), (1368, 3304), (520, 264), (72, 40)])
 @pytest.mark.parametrize("K", [8, 64, 72, 128, 200, 264])
