@@ -809,9 +809,15 @@ __global__ void ce_f32_kernel(const float* z, const int32_t* labels, int rows, i
   if (lane == 0) loss_rows[row] = loss;
 }
 
-// The same with the mean in one workgroup, for few rows (two a wave): the
-// second launch costs more than the rows.
+// The same with the mean in one workgroup, where that costs less than the
+// second launch (4 us): one CU walks all rows, and a wave two of them beyond
+// 16.  32 rows of 100 classes take 6.8 us here and 3.8 spread out, of 1000
+// classes 29.0 and 13.2, of 50000 classes 1391 and 553; 16 rows of 1000 take
+// 15.5 and 12.6; up to four rows, one workgroup either way, the same.
 constexpr int CE_F32_ONE = 32;
+static bool ce_f32_one(int rows, int V) {
+  return rows <= 4 || (rows <= CE_F32_ONE && (int64_t)rows * V <= (rows <= 16 ? 16384 : 4096));
+}
 __global__ __launch_bounds__(1024) void ce_f32_mean_kernel(const float* z, const int32_t* labels, int rows, int V,
                                                            float* dz, float* loss_rows, float* loss_out) {
   __shared__ float loss[CE_F32_ONE];
@@ -828,7 +834,7 @@ __global__ __launch_bounds__(1024) void ce_f32_mean_kernel(const float* z, const
 
 hipError_t launch_ce_f32(const float* logits, const int32_t* labels, int rows, int V, float* dlogits,
                          float* loss_rows, float* loss_out, hipStream_t s) {
-  if (loss_out && rows <= CE_F32_ONE) {
+  if (loss_out && ce_f32_one(rows, V)) {
     ce_f32_mean_kernel<<<1, 1024, 0, s>>>(logits, labels, rows, V, dlogits, loss_rows, loss_out);
     return hipGetLastError();
   }

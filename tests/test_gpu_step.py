@@ -83,6 +83,62 @@ def test_mlp_two_streams_equal_one_stream():
     assert np.array_equal(outs[0], outs[1])
 
 
+def mlp_one_step(dims, batch, two_streams=True, seed=0):
+    """One SGD step of a float32 MLP of any widths against the oracle, every
+    gradient, parameter and momentum at 1e-5 (float32 sums of at most 2048
+    terms).  The first input is +-1 and drives every hidden unit well away
+    from zero, on or off with its sign, so that no ReLU stands at its edge."""
+    rng = np.random.default_rng(seed + sum(dims) + batch)
+    n = len(dims) - 1
+    x = rng.standard_normal((batch, dims[0])).astype(np.float32)
+    x[:, 0] = rng.choice([-1.0, 1.0], batch)
+    y = rng.integers(0, dims[-1], batch).astype(np.int32)
+    params, prev = {}, None
+    for i in range(n):
+        w = rng.standard_normal((dims[i + 1], dims[i])) * (1.0 if i == n - 1 else 0.1) / np.sqrt(dims[i])
+        sign = rng.choice([-1.0, 1.0], dims[i + 1])
+        if i < n - 1 and i == 0:
+            w[:, 0] = 4.0 * sign
+        elif i < n - 1:
+            w += np.outer(sign, prev) * 4.0 / dims[i]
+        params[f"fc{i + 1}.w"] = w.astype(np.float32)
+        params[f"fc{i + 1}.b"] = (0.02 * rng.standard_normal(dims[i + 1])).astype(np.float32)
+        prev = sign
+    h = x.astype(np.float64)
+    for i in range(n - 1):
+        h = h @ params[f"fc{i + 1}.w"].astype(np.float64).T + params[f"fc{i + 1}.b"]
+        assert np.abs(h).min() > 0.1
+        h = np.maximum(h, 0.0)
+    peer = S.peer_of(params, 0.01)
+    m = LU.Model(LU.mlp_config(dims, batch), "sgd", two_streams=two_streams)
+    m.load("params", params)
+    m.load("peers", peer)
+    xd, yd = torch.from_numpy(x).to(DEV), torch.from_numpy(y).to(DEV)
+    loss = torch.zeros(1, dtype=torch.float32, device=DEV)
+    torch.cuda.synchronize()
+    LU.layup_step(m.ctx, yd, xd, LU.hparams("sgd", 0.05, 0.9, 0.0), 0.5, 0, loss)
+    op = {k: v.astype(np.float64) for k, v in params.items()}
+    om = {k: np.zeros_like(v) for k, v in op.items()}
+    oloss, ograds, _, _ = O.mlp_step(op, om, {k: v.astype(np.float64) for k, v in peer.items()}, x, y,
+                                     dict(optim="sgd", lr=0.05, momentum=0.9, weight_decay=0.0), 0.5)
+    m.synchronize()
+    assert abs(loss.item() - oloss) <= 1e-5 * abs(oloss) + 1e-6
+    g, p, mom = m.read("grads"), m.read("params"), m.read("m")
+    for k in op:
+        compare(g[k], ograds[k].reshape(g[k].shape), 1e-5, f"grad {k}")
+        compare(p[k], op[k].reshape(p[k].shape), 1e-5, f"param {k}")
+        compare(mom[k], om[k].reshape(mom[k].shape), 1e-5, f"momentum {k}")
+    m.close()
+
+
+@pytest.mark.parametrize("batch", [1, 4, 5, 16, 17, 32, 33])
+@pytest.mark.parametrize("classes", [2, 37, 130, 1025, 5000])
+def test_mlp_cross_entropy_rows_and_classes(batch, classes):
+    """Both forms of the float32 cross-entropy (with the mean in one workgroup,
+    or spread out with a second launch) at the edges of the rule between them."""
+    mlp_one_step((24, classes), batch)
+
+
 # ------------------------------------------------------------------ GPT
 
 def check_adamw_params(got, ref, m_gpu, g_ref, cfg, name):
