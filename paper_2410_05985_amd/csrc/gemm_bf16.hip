@@ -1216,7 +1216,7 @@ struct Plan {
   int64_t run = ANY_RUN;
   float us = 3.4e38f;
 };
-static Plan choose(const Gemm* g, int n, bool group, bool beside) {
+static Plan choose(const Gemm* g, int n, bool group, bool beside, int only_split = 0) {
   const bool splittable = g[0].batch == 1 && (g[0].epi == EPI_F32 || g[0].epi == EPI_UPDATE) && g[0].splitk_ws;
   double outputs = 0.0;
   size_t per_split = 0;
@@ -1237,6 +1237,7 @@ static Plan choose(const Gemm* g, int n, bool group, bool beside) {
     for (int i = 0; i < n; ++i) tiles += cdiv(g[i].M, t.bm) * cdiv(g[i].N, t.bn) * g[i].batch;
     for (int sp = 1; sp <= std::max<int64_t>(1, max_split); ++sp) {
       if (sp > 1 && (sp * per_split > g[0].splitk_ws_bytes || g[0].M > 65535)) break;
+      if (only_split && sp != only_split) continue;
       const int64_t run = sp > 1 ? cdiv(cdiv(g[0].K, sp), 32) * 32 : g[0].K;
       const bool flush = run > limit;
       if (flush && !can_flush(t.bm, t.bn, g[0].a_kmajor)) continue;
@@ -1251,7 +1252,11 @@ static Plan choose(const Gemm* g, int n, bool group, bool beside) {
 }
 
 hipError_t launch_gemm_bf16_group(const Gemm* g, int n, const LnSum* ln, int n_ln, bool beside, hipStream_t s) {
-  const Plan p = choose(g, n, true, beside);
+  // The split of K and the run limit fix the order of the sums, the tile does
+  // not: with the split chosen as for the launch beside another stream, the
+  // results are the same bit for bit on one stream and on two.
+  Plan p = choose(g, n, true, true);
+  if (!beside) p = choose(g, n, true, false, p.splits);
   return launch_gemm_bf16_group_cfg(g, n, ln, n_ln, p.cfg, p.splits, s);
 }
 

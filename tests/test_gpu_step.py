@@ -307,6 +307,46 @@ def test_gpt_two_streams_equal_one_stream_and_repeatable(cfg):
             assert torch.equal(a, b), (run, name)
 
 
+def _seeded_model(cfg, two_streams):
+    """A model whose buffers are drawn on the GPU (wide stacks; padding stays zero)."""
+    m = LU.Model(LU.gpt_config(cfg.n_layer, cfg.d_model, cfg.n_head, cfg.d_ff, cfg.seq, cfg.batch, cfg.vocab), "adamw",
+                 two_streams=two_streams)
+    g = torch.Generator(device=DEV).manual_seed(17)
+    for t in m.infos:
+        s = slice(t["offset"], t["offset"] + t["numel"])
+        m.params[s].normal_(1.0 if t["name"].endswith(".g") else 0.0, 0.02, generator=g)
+        m.peers[s].normal_(0.0, 0.02, generator=g)
+    td = torch.randint(0, cfg.vocab, (cfg.batch, cfg.seq + 1), device=DEV, dtype=torch.int32, generator=g)
+    torch.cuda.synchronize()
+    LU.layup_refresh_shadow(m.ctx)
+    m.synchronize()
+    return m, td
+
+
+@pytest.mark.parametrize("schedule", [LU.LAYUP_SCHEDULE_LAYERWISE, LU.LAYUP_SCHEDULE_FUSED_DW])
+@pytest.mark.parametrize("width,heads,ff", [
+    (640, 10, 2560),   # the dW launch beside the dX chain: another tile than alone, the same sums
+    (2048, 16, 4096),  # so much work that the dW launch stays on the compute stream, the update on its own
+])
+def test_gpt_wide_two_streams_equal_one_stream(width, heads, ff, schedule):
+    """Three blocks of 8192 tokens, two steps: where the dW products run and
+    which tiles they take changes no bit, in either schedule."""
+    cfg = S.GPTConfig(n_layer=3, d_model=width, n_head=heads, d_ff=ff, seq=1024, batch=8, vocab=500, name="wide")
+    outs = []
+    for two in (True, False):
+        m, td = _seeded_model(cfg, two)
+        for s in range(2):
+            hp, _ = gpt_hp(cfg, s + 1)
+            LU.layup_step_ex(m.ctx, td, None, hp, cfg.alpha, schedule=schedule)
+        m.synchronize()
+        outs.append([t.clone() for t in (m.params, m.m, m.v, m.grads, m.params_bf16)])
+        m.close()
+        del m
+    assert torch.all(torch.isfinite(outs[0][0]))
+    for name, a, b in zip(("params", "m", "v", "grads", "bf16 copy"), outs[0], outs[1]):
+        assert torch.equal(a, b), name
+
+
 def test_gpt_repeated_and_out_of_vocabulary_tokens_two_streams_equal_one_stream():
     """A batch of few distinct tokens, repeated, with some outside the
     vocabulary (which gather no embedding row and get no gradient): the
