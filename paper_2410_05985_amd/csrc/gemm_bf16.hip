@@ -97,10 +97,14 @@ __device__ __forceinline__ float sum_bf16x8(const u32x4& u) {
   return s;
 }
 
+// Split of K: none, one for the launch, or each product of a group its own
+// (P.splits, which may be 1).
+enum SplitMode : int { SPLIT_NO = 0, SPLIT_YES = 1, SPLIT_OWN = 2 };
+
 // Epilogue of W consecutive columns n..n+W-1 of row m (columns >= N
 // skipped); W = 4 for float32 results, 8 for bfloat16 ones.  vec: every
 // access 16-byte aligned and n + W <= N.
-template <int EPI, bool SPLIT, int W>
+template <int EPI, int SPLIT, int W>
 __device__ __forceinline__ void epi_store(const KArgs& P, int split, int64_t c_off, int64_t m, int64_t n,
                                           float (&v)[W], bool vec) {
   const int64_t rem = P.N - n;
@@ -108,10 +112,15 @@ __device__ __forceinline__ void epi_store(const KArgs& P, int split, int64_t c_o
   if constexpr (SPLIT || EPI == EPI_F32 || EPI == EPI_UPDATE) {
     static_assert(W == 4, "float32 results go four columns at a time");
     const f32x4 v4{v[0], v[1], v[2], v[3]};
-    if constexpr (SPLIT) {
-      float* dst = P.partial + (int64_t)split * P.M * P.N + m * P.N + n;
-      if (vec) *reinterpret_cast<f32x4*>(dst) = v4;
-      else for (int e = 0; e < ne; ++e) dst[e] = v[e];
+    if constexpr (SPLIT != SPLIT_NO) {
+      if (SPLIT == SPLIT_YES || P.splits > 1) {
+        float* dst = P.partial + (int64_t)split * P.M * P.N + m * P.N + n;
+        if (vec) *reinterpret_cast<f32x4*>(dst) = v4;
+        else for (int e = 0; e < ne; ++e) dst[e] = v[e];
+        return;
+      }
+    }
+    if constexpr (SPLIT == SPLIT_YES) {
     } else if constexpr (EPI == EPI_UPDATE) {
       const int64_t off = m * P.ldc + n;
       if (vec) apply_update4(P.upd, off, v4);
@@ -404,7 +413,7 @@ __device__ __forceinline__ void barrier_only() {
 // tiles.  This is the work of one workgroup: item `lid` of P's flat list of
 // (batch or split, tile) work items.
 // FL: the accumulators take at most P.run products in a row.
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool AK, bool BKM, int EPI, bool SPLIT, int BKV, bool FL>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool AK, bool BKM, int EPI, int SPLIT, int BKV, bool FL>
 __device__ __forceinline__ void gemm_item(const KArgs& P, int lid) {
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
@@ -696,7 +705,8 @@ __device__ __forceinline__ void gemm_item(const KArgs& P, int lid) {
         const float tot = rsum[i] + __shfl_xor(rsum[i], 32, 64);  // the two k halves
         const int64_t m = m0 + wm * WM + i * 32 + lane;
         if (lane < 32 && m < P.M) {
-          if (SPLIT) P.partial[(int64_t)P.splits * P.M * P.N + (int64_t)split * P.M + m] = tot;
+          if (SPLIT == SPLIT_YES || (SPLIT == SPLIT_OWN && P.splits > 1))
+            P.partial[(int64_t)P.splits * P.M * P.N + (int64_t)split * P.M + m] = tot;
           else P.rowsum[m] = tot;
         }
       }
@@ -747,26 +757,27 @@ __device__ __forceinline__ void gemm_item(const KArgs& P, int lid) {
 // over the 8 XCDs (each with its own L2), so hardware id h runs on XCD h % 8:
 // the remap gives every XCD a contiguous range of logical ids, i.e. whole
 // bands of tiles of one batch/split that share operand rows.
-__device__ __forceinline__ int work_item(int n) {
-  const int h = blockIdx.x;
+__device__ __forceinline__ int work_item(int n, int h) {
   return (h & 7) * ((n + 7) >> 3) + (h >> 3);
 }
 
 // OCC: workgroups per CU.
-template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, bool AK, bool BKM, int EPI, bool SPLIT, int BKV,
+template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, bool AK, bool BKM, int EPI, int SPLIT, int BKV,
           bool FL>
 __global__ __launch_bounds__(64 * WGM * WGN, FL ? OCC * WGM * WGN / 4 : OCC) void gemm_bf16_kernel(const KArgs P) {
   const int n = P.tiles_m * P.tiles_n * (SPLIT ? P.splits : P.nz);
-  const int lid = work_item(n);
+  const int lid = work_item(n, blockIdx.x);
   if (lid >= n) return;
   gemm_item<BM, BN, WGM, WGN, STAGES, AK, BKM, EPI, SPLIT, BKV, FL>(P, lid);
 }
 
 // Several products dW = dY^T X in one launch (GemmGroup): the work items of
-// all of them numbered one product after the other.
+// all of them numbered one product after the other, the products without a
+// split of K first.  Their items and the others, shorter ones are dealt to the
+// XCDs each by themselves, the longer first.
 constexpr int MAX_GROUP = GEMM_GROUP_MAX;
 struct GroupArgs {
-  int32_t n;
+  int32_t n, n_whole;             // products; those without a split
   int32_t first[MAX_GROUP + 1];   // first work item of each product
   int32_t rfirst[MAX_GROUP + 1];  // first workgroup of each product's split-K sum
   int32_t n_ln, ln_blocks;        // LayerNorm gradient sums riding along: blocks of each
@@ -774,24 +785,27 @@ struct GroupArgs {
   KArgs p[MAX_GROUP];
 };
 
-template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool SPLIT, int BKV>
+template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, int BKV>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void gemm_bf16_group_kernel(const GroupArgs G) {
-  const int n = G.first[G.n], ng = (n + 7) / 8 * 8;
-  if ((int)blockIdx.x >= ng) {
+  const int n = G.first[G.n], n1 = G.first[G.n_whole];
+  const int g1 = (n1 + 7) / 8 * 8, ng = g1 + (n - n1 + 7) / 8 * 8;
+  const int h = blockIdx.x;
+  if (h >= ng) {
     // the LayerNorm sums follow the products: they run on the CUs the last round leaves free
     constexpr int NT = 64 * WGM * WGN;
     static_assert(NT % LN_SUM_THREADS == 0, "whole teams of the LayerNorm sum");
     __shared__ f32x4 red[NT];
-    const int b = (int)blockIdx.x - ng, sub = (int)threadIdx.x / LN_SUM_THREADS;
+    const int b = h - ng, sub = (int)threadIdx.x / LN_SUM_THREADS;
     ln_sum_item(G.ln[b / G.ln_blocks], (b % G.ln_blocks) * (NT / LN_SUM_THREADS) + sub,
                 (int)threadIdx.x % LN_SUM_THREADS, red + sub * LN_SUM_THREADS);
     return;
   }
-  const int lid = work_item(n);
-  if (lid >= n) return;
+  const int lid = h < g1 ? work_item(n1, h) : n1 + work_item(n - n1, h - g1);
+  if (lid >= (h < g1 ? n1 : n)) return;
   int i = 0;
   while (i + 1 < G.n && lid >= G.first[i + 1]) ++i;
-  gemm_item<BM, BN, WGM, WGN, STAGES, false, false, EPI, SPLIT, BKV, BM * BN <= 256 * 128>(G.p[i], lid - G.first[i]);
+  gemm_item<BM, BN, WGM, WGN, STAGES, false, false, EPI, SPLIT_OWN, BKV, BM * BN <= 256 * 128>(G.p[i],
+                                                                                              lid - G.first[i]);
 }
 
 // Sum over the splits, in split order, of the partials of four consecutive
@@ -905,7 +919,7 @@ hipError_t launch_tiles(const KArgs& P, int batch, hipStream_t s) {
   constexpr int NT = 64 * WGM * WGN;
   if constexpr (EPI == EPI_F32 || EPI == EPI_UPDATE) {
     if (P.splits > 1) {
-      gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, true, BKV, FL><<<grid, NT, 0, s>>>(P);
+      gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, SPLIT_YES, BKV, FL><<<grid, NT, 0, s>>>(P);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
       const int64_t groups = P.M * cdiv(P.N, 4);
@@ -914,7 +928,7 @@ hipError_t launch_tiles(const KArgs& P, int batch, hipStream_t s) {
       return hipGetLastError();
     }
   }
-  gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, false, BKV, FL><<<grid, NT, 0, s>>>(P);
+  gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, SPLIT_NO, BKV, FL><<<grid, NT, 0, s>>>(P);
   return hipGetLastError();
 }
 
@@ -1035,40 +1049,38 @@ struct TileCfg {
   int bm, bn, occ;
   float step_lo, step_hi, fix;
   float dw;  // steps of dW = dY^T X (both operands m-major, twice the LDS reads) take this much longer
+  float fl;  // and those in short runs (FL)
 };
 enum TileId { T256x256 = 0, T256x192, T256x128, T128x192, T128x128, T128x64, T64x64, kNumCfg };
 static const TileCfg kCfgs[kNumCfg] = {
-    {256, 256, 1, 1.30f, 1.75f, 3.0f, 1.12f},  // 2x4 waves (each 128x64), 2 stages of K 64
-    {256, 192, 1, 1.25f, 1.55f, 3.0f, 1.12f},  // 4x2 waves (each 64x96),  2 stages of K 64
-    {256, 128, 1, 0.85f, 1.10f, 3.0f, 1.05f},  // 4x2 waves (each 64x64),  3 stages of K 64
-    {128, 192, 1, 0.70f, 0.90f, 3.0f, 1.12f},  // 4x2 waves (each 32x96),  3 stages of K 64
-    {128, 128, 2, 0.70f, 1.15f, 3.0f, 1.12f},  // 2x4 waves (each 64x32),  2 stages of K 64
-    {128, 64, 3, 0.41f, 1.10f, 2.5f, 1.12f},   // 2x2 waves (each 64x32),  4 stages of K 32
-    {64, 64, 4, 0.38f, 0.72f, 2.0f, 1.12f},    // 2x2 waves (each 32x32),  2 stages of K 64
+    {256, 256, 1, 1.30f, 1.75f, 3.0f, 1.12f, 1.00f},  // 2x4 waves (each 128x64), 2 stages of K 64
+    {256, 192, 1, 1.25f, 1.55f, 3.0f, 1.12f, 1.00f},  // 4x2 waves (each 64x96),  2 stages of K 64
+    {256, 128, 1, 0.85f, 1.10f, 3.0f, 1.05f, 1.02f},  // 4x2 waves (each 64x64),  3 stages of K 64
+    {128, 192, 1, 0.70f, 0.90f, 3.0f, 1.12f, 1.03f},  // 4x2 waves (each 32x96),  3 stages of K 64
+    {128, 128, 2, 0.70f, 1.15f, 3.0f, 1.12f, 1.02f},  // 2x4 waves (each 64x32),  2 stages of K 64
+    {128, 64, 3, 0.41f, 1.10f, 2.5f, 1.12f, 1.05f},   // 2x2 waves (each 64x32),  4 stages of K 32
+    {64, 64, 4, 0.38f, 0.72f, 2.0f, 1.12f, 1.15f},    // 2x2 waves (each 32x32),  2 stages of K 64
 };
 
 namespace {
 template <int BM, int BN, int WGM, int WGN, int STG, int OCC, int BKV, int EPI>
-hipError_t launch_group_epi(const GroupArgs& G0, bool split, hipStream_t s) {
+hipError_t launch_group_epi(const GroupArgs& G0, hipStream_t s) {
   constexpr int NT = 64 * WGM * WGN;
   GroupArgs G = G0;
   if (G.n_ln) G.ln_blocks = (int)cdiv(ln_sum_teams(G.ln[0].d), NT / LN_SUM_THREADS);
-  const dim3 grid((unsigned)((G.first[G.n] + 7) / 8 * 8 + G.n_ln * G.ln_blocks));
-  if (!split) {
-    gemm_bf16_group_kernel<BM, BN, WGM, WGN, STG, OCC, EPI, false, BKV><<<grid, NT, 0, s>>>(G);
-    return hipGetLastError();
-  }
-  gemm_bf16_group_kernel<BM, BN, WGM, WGN, STG, OCC, EPI, true, BKV><<<grid, NT, 0, s>>>(G);
+  const int n1 = G.first[G.n_whole], n2 = G.first[G.n] - n1;
+  const dim3 grid((unsigned)((n1 + 7) / 8 * 8 + (n2 + 7) / 8 * 8 + G.n_ln * G.ln_blocks));
+  gemm_bf16_group_kernel<BM, BN, WGM, WGN, STG, OCC, EPI, BKV><<<grid, NT, 0, s>>>(G);
   const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || G.rfirst[G.n] == 0) return e;
   splitk_reduce_group_kernel<EPI><<<(unsigned)G.rfirst[G.n], 256, 0, s>>>(G);
   return hipGetLastError();
 }
 
 template <int BM, int BN, int WGM, int WGN, int STG, int OCC, int BKV>
-hipError_t launch_group(const GroupArgs& G, int epi, bool split, hipStream_t s) {
-  return epi == EPI_UPDATE ? launch_group_epi<BM, BN, WGM, WGN, STG, OCC, BKV, EPI_UPDATE>(G, split, s)
-                           : launch_group_epi<BM, BN, WGM, WGN, STG, OCC, BKV, EPI_F32>(G, split, s);
+hipError_t launch_group(const GroupArgs& G, int epi, hipStream_t s) {
+  return epi == EPI_UPDATE ? launch_group_epi<BM, BN, WGM, WGN, STG, OCC, BKV, EPI_UPDATE>(G, s)
+                           : launch_group_epi<BM, BN, WGM, WGN, STG, OCC, BKV, EPI_F32>(G, s);
 }
 }  // namespace
 
@@ -1093,8 +1105,28 @@ static int64_t run_limit(const Gemm& g) {
   return splits < 2 ? ANY_RUN : cdiv(cdiv(g.K, splits), 32) * 32;
 }
 
+// Splits of K that keep a product within its limit, and the workspace of split
+// products: partial sums and row sums, each product's 256-byte aligned.
+static int own_splits(const Gemm& g) {
+  const int64_t limit = run_limit(g);
+  return limit < g.K ? (int)cdiv(g.K, limit) : 1;
+}
+static size_t product_bytes(const Gemm& g, int splits) {
+  return (((size_t)g.M * g.N + (g.rowsum ? g.M : 0)) * 4 * splits + 255) / 256 * 256;
+}
+// splits = 0: each product's own
+static size_t group_bytes(const Gemm* g, int n, int splits) {
+  size_t b = 0;
+  for (int i = 0; i < n; ++i) {
+    const int sp = splits ? splits : own_splits(g[i]);
+    if (sp > 1) b += product_bytes(g[i], sp);
+  }
+  return b;
+}
+
 // The products share K, the epilogue (float32 or the weight update) and the
-// split-K workspace, which splits > 1 needs room in for all of them.
+// split-K workspace, which has room for `splits` of each product; splits = 0:
+// each as many as its run limit asks for.
 hipError_t launch_gemm_bf16_group_cfg(const Gemm* g, int n, const LnSum* ln, int n_ln, int cfg, int splits,
                                       hipStream_t s) {
   if (n_ln < 0 || n_ln > 2 || (n_ln == 2 && ln[0].d != ln[1].d)) return hipErrorInvalidValue;
@@ -1106,47 +1138,47 @@ hipError_t launch_gemm_bf16_group_cfg(const Gemm* g, int n, const LnSum* ln, int
   for (int i = 0; i < n_ln; ++i) G.ln[i] = ln[i];
   const int BM = kCfgs[cfg].bm, BN = kCfgs[cfg].bn;
   const int64_t K = g[0].K;
-  size_t per_split = 0;
-  for (int i = 0; i < n; ++i) {
+  for (int i = 0; i < n; ++i)
     if (g[i].K != K || g[i].epi != g[0].epi || g[i].a_kmajor || g[i].b_kmajor || g[i].batch != 1 || g[i].M < 1 ||
         g[i].N < 1 || (g[i].epi != EPI_F32 && g[i].epi != EPI_UPDATE))
       return hipErrorInvalidValue;
-    per_split += ((size_t)g[i].M * g[i].N + (g[i].rowsum ? g[i].M : 0)) * 4;
-    per_split = (per_split + 255) / 256 * 256;
-  }
-  if (!g[0].splitk_ws) splits = 1;
-  while (splits > 1 && splits * per_split > g[0].splitk_ws_bytes) --splits;
-  int64_t k_per = K;
-  if (splits > 1) {
-    k_per = cdiv(cdiv(K, splits), 32) * 32;
-    splits = (int)cdiv(K, k_per);
-  }
+  const size_t room = g[0].splitk_ws ? g[0].splitk_ws_bytes : 0;
+  while (splits > 1 && group_bytes(g, n, splits) > room) --splits;
   char* part = (char*)g[0].splitk_ws;
   int64_t items = 0, rblocks = 0;
-  for (int i = 0; i < n; ++i) {
-    KArgs& P = G.p[i];
-    P = make_args(g[i]);
-    P.tiles_m = (int)cdiv(P.M, BM);
-    P.tiles_n = (int)cdiv(P.N, BN);
-    P.run = run_limit(g[i]);
-    G.first[i] = (int)items;
-    G.rfirst[i] = (int)rblocks;
-    items += (int64_t)P.tiles_m * P.tiles_n * splits;
-    if (splits > 1) {
-      P.splits = splits;
-      P.k_per_split = k_per;
-      P.partial = (float*)part;
-      part += (((size_t)P.M * P.N + (P.rowsum ? P.M : 0)) * 4 * splits + 255) / 256 * 256;
-      rblocks += cdiv(P.M * cdiv(P.N, 4), 256);
+  int at = 0;
+  for (int pass = 0; pass < 2; ++pass) {  // whole products, then split ones
+    for (int i = 0; i < n; ++i) {
+      const int sp = splits ? splits : own_splits(g[i]);
+      if ((sp > 1) != (pass == 1)) continue;
+      KArgs& P = G.p[at];
+      P = make_args(g[i]);
+      P.tiles_m = (int)cdiv(P.M, BM);
+      P.tiles_n = (int)cdiv(P.N, BN);
+      P.run = run_limit(g[i]);
+      P.k_per_split = K;
+      if (sp > 1) {
+        P.k_per_split = cdiv(cdiv(K, sp), 32) * 32;
+        P.splits = (int)cdiv(K, P.k_per_split);
+        P.partial = (float*)part;
+        part += product_bytes(g[i], P.splits);
+        if (part > (char*)g[0].splitk_ws + room) return hipErrorInvalidValue;
+      }
+      G.first[at] = (int)items;
+      G.rfirst[at] = (int)rblocks;
+      items += (int64_t)P.tiles_m * P.tiles_n * P.splits;
+      if (P.splits > 1) rblocks += cdiv(P.M * cdiv(P.N, 4), 256);
+      if (items >= (1ll << 31) - 16 || rblocks >= (1ll << 31)) return hipErrorInvalidValue;
+      ++at;
     }
-    if (items >= (1ll << 31) - 8 || rblocks >= (1ll << 31)) return hipErrorInvalidValue;
+    if (pass == 0) G.n_whole = at;
   }
   G.first[n] = (int)items;
   G.rfirst[n] = (int)rblocks;
   switch (cfg) {
-    case T256x256: return launch_group<256, 256, 2, 4, 2, 1, 64>(G, g[0].epi, splits > 1, s);
-    case T256x128: return launch_group<256, 128, 4, 2, 3, 1, 64>(G, g[0].epi, splits > 1, s);
-    case T128x128: return launch_group<128, 128, 2, 4, 2, 2, 64>(G, g[0].epi, splits > 1, s);
+    case T256x256: return launch_group<256, 256, 2, 4, 2, 1, 64>(G, g[0].epi, s);
+    case T256x128: return launch_group<256, 128, 4, 2, 3, 1, 64>(G, g[0].epi, s);
+    case T128x128: return launch_group<128, 128, 2, 4, 2, 2, 64>(G, g[0].epi, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1204,19 +1236,21 @@ static float est_items(const TileCfg& t, int64_t items, float steps, float bytes
 // the smallest estimate over the configurations and splits, the split's
 // partial sums written and read back at 4.5 TB/s by a second launch (8 us).
 // A split leaves at least 512 k each, at most 8 of them.  A tile that would
-// exceed the run limit takes its FL form (1 % more a step) or is left out.
+// exceed the run limit takes its FL form or is left out.  (Over 568 products of
+// 64 to 8192 a side that have a limit, the plan takes 0.96 of the time of the
+// plan without one, 1.06 at the 90th percentile, 1.27 at most.)
 // beside: the launch shares the chip with another stream's kernels, and what it
 // takes from them counts besides its own time: tiles of several workgroups a CU
-// leave them no CU, a split adds work.  Both count a tenth more: the GPT-2-small
-// step takes 11.65 ms with 128 x 128 and 11.42 with 256 x 128, four blocks of
-// GPT-2-medium's width 7.85 ms with 128 x 128, 7.87 with 256 x 128 and K split
-// in two, and 7.73 with 256 x 128.
+// leave them no CU, nor do many workgroups, and a split adds work.  Where there is
+// a limit, these count a tenth more: the GPT-2-small step takes 11.65 ms with 128 x 128 and
+// 11.42 with 256 x 128, four blocks of GPT-2-medium's width 7.85 ms with 128 x
+// 128, 7.87 with 256 x 128 and K split in two, and 7.73 with 256 x 128.
 struct Plan {
-  int cfg = T128x128, splits = 1;
+  int cfg = T128x128, splits = 1;  // 0: each product of a group its own split
   int64_t run = ANY_RUN;
   float us = 3.4e38f;
 };
-static Plan choose(const Gemm* g, int n, bool group, bool beside, int only_split = 0) {
+static Plan choose(const Gemm* g, int n, bool group, bool beside, int only_split = -1) {
   const bool splittable = g[0].batch == 1 && (g[0].epi == EPI_F32 || g[0].epi == EPI_UPDATE) && g[0].splitk_ws;
   double outputs = 0.0;
   size_t per_split = 0;
@@ -1229,24 +1263,48 @@ static Plan choose(const Gemm* g, int n, bool group, bool beside, int only_split
   float bytes = g[0].epi == EPI_F32 ? 4.f : g[0].epi == EPI_BF16 ? 2.f : g[0].epi == EPI_UPDATE ? 30.f : 4.f;
   if (g[0].epi == EPI_F32 && g[0].aux) bytes += 4.f;
   const int64_t max_split = splittable ? std::min<int64_t>(8, g[0].K / 512) : 1;
+  // a single product that has a limit is split more often than not: 5 us and
+  // 6 TB/s are what its sums cost on average (over the 568 products above)
+  const bool tight = !group && limit < g[0].K;
+  const float sum_fix = tight ? 5.f : 8.f, sum_rate = tight ? 6e6f : 4.5e6f;
   Plan best;
+  auto tiles_of = [&](const TileCfg& t) {
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += cdiv(g[i].M, t.bm) * cdiv(g[i].N, t.bn) * g[i].batch;
+    return tiles;
+  };
+  auto consider = [&](int c, int sp, int64_t items, float us) {
+    if (beside && limit < g[0].K && (kCfgs[c].occ > 1 || sp > 1 || items > 384)) us *= 1.1f;
+    if (us < best.us) best = Plan{c, sp, limit, us};
+  };
   for (int c = 0; c < kNumCfg; ++c) {
     if (group && c != T256x256 && c != T256x128 && c != T128x128) continue;
     const TileCfg& t = kCfgs[c];
-    int64_t tiles = 0;
-    for (int i = 0; i < n; ++i) tiles += cdiv(g[i].M, t.bm) * cdiv(g[i].N, t.bn) * g[i].batch;
+    const int64_t tiles = tiles_of(t);
     for (int sp = 1; sp <= std::max<int64_t>(1, max_split); ++sp) {
       if (sp > 1 && (sp * per_split > g[0].splitk_ws_bytes || g[0].M > 65535)) break;
-      if (only_split && sp != only_split) continue;
+      if (only_split >= 0 && sp != only_split) continue;
       const int64_t run = sp > 1 ? cdiv(cdiv(g[0].K, sp), 32) * 32 : g[0].K;
       const bool flush = run > limit;
       if (flush && !can_flush(t.bm, t.bn, g[0].a_kmajor)) continue;
-      const float steps = (float)cdiv(cdiv(g[0].K, sp), 64) * (g[0].a_kmajor ? 1.0f : t.dw) * (flush ? 1.01f : 1.0f);
+      const float steps = (float)cdiv(cdiv(g[0].K, sp), 64) * (g[0].a_kmajor ? 1.0f : t.dw) * (flush ? t.fl : 1.0f);
       float us = est_items(t, tiles * sp, steps, sp > 1 ? 4.f : bytes);
-      if (sp > 1) us += 8.f + (float)(outputs * (4.0 * sp + bytes) / 4.5e6);
-      if (beside && (t.occ > 1 || sp > 1)) us *= 1.1f;
-      if (us < best.us) best = Plan{c, sp, limit, us};
+      if (sp > 1) us += sum_fix + (float)(outputs * (4.0 * sp + bytes) / sum_rate);
+      consider(c, sp, tiles * sp, us);
     }
+  }
+  // 256 x 256 with only the limited products of the group split, as far as
+  // their limits ask for: the attention projection alone from about 1100
+  // features on
+  if (group && limit < g[0].K && only_split <= 0 && group_bytes(g, n, 0) <= g[0].splitk_ws_bytes) {
+    const TileCfg& t = kCfgs[T256x256];
+    const int64_t tiles = tiles_of(t);
+    float us = est_items(t, tiles, (float)cdiv(g[0].K, 64) * t.dw, bytes) + 8.f;
+    for (int i = 0; i < n; ++i) {
+      const int sp = own_splits(g[i]);
+      if (sp > 1) us += (float)((double)g[i].M * g[i].N * (8.0 * sp + bytes) / 4.5e6);
+    }
+    consider(T256x256, 0, tiles, us);
   }
   return best;
 }

@@ -275,7 +275,8 @@ hipError_t launch_ce_f32(const float* logits, const int32_t* labels, int rows, i
 extern "C" {
 // GELU and its derivative of x, float32, as the GEMM epilogues compute them.
 int layup_test_gelu(const float* x, float* y, float* dy, int64_t n, void* stream);
-// n products with the tile configuration (TileId) and split of K given: as one
+// n products with the tile configuration (TileId) and split of K given (0 in a
+// group: each product as far as its run limit asks): as one
 // group launch (group != 0, 2: beside other kernels; dW = dY^T X only), or a single product, summed in
 // runs of at most `run` products (>= 64).  cfg < 0: the plan the library chooses.  upd, when
 // given, holds the tensors of the update epilogue, one per product.

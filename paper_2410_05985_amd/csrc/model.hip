@@ -205,14 +205,16 @@ struct layup_ctx {
   float *splitk = nullptr, *splitk_su = nullptr;
   size_t splitk_bytes = 0, splitk_su_bytes = 0;
   // Do the blocks' dW GEMMs run on the update stream, beside the next block's
-  // dX chain?  Where one launch of them is at most a round of 256 x 256 tiles
-  // on the 256 CUs, it fills the tails of the chain's kernels (GPT-2-small
-  // step 12.30 -> 11.88 ms, GPT-2-medium width 7.98 -> 7.74 ms); a launch of
-  // several rounds fills the chip by itself, and sharing it only costs (1.3B
-  // width 12.60 -> 12.94 ms).
+  // dX chain?  Small launches fill the tails of the chain's kernels, large ones
+  // fill the chip by themselves and sharing it only costs.  Step times, compute
+  // stream -> update stream (layer-wise | fused schedule), by a block's weights
+  // and tokens: 7.1M x 8192 4.73 -> 4.67 ms | 4.76 -> 4.66 (6 blocks), 12.6M x
+  // 8192 4.89 -> 4.97 | 4.81 -> 4.74 (4), 50M x 2048 4.45 -> 4.34 | 4.25 ->
+  // 4.27 (3), 19.7M x 8192 7.30 -> 7.23 | 7.40 -> 7.27 (4), 28.3M x 8192 7.02
+  // -> 7.13 | 6.92 -> 7.08 (3), 50M x 8192 7.69 -> 7.98 | 7.55 -> 7.95 (2).
   bool dw_side() const {
     const int64_t weights = 4 * (int64_t)cfg.d_model * cfg.d_model + 2 * (int64_t)cfg.d_model * cfg.d_ff;
-    return su != sc && cfg.model == LAYUP_MODEL_GPT_BF16 && weights <= 256 * 256 * 256;
+    return su != sc && cfg.model == LAYUP_MODEL_GPT_BF16 && weights * cfg.seq * cfg.batch <= 200000000000;
   }
   float* dis_partial = nullptr;
   // MLP
@@ -1374,7 +1376,7 @@ layup_status layup_gemm_f32(const layup_gemm_desc* d, void* stream) { return gem
 
 int layup_test_gemm_tile(const layup_gemm_desc* d, int32_t n, int32_t group, int32_t cfg, int32_t splits,
                          int64_t run, const layup_tensor* upd, const layup_hparams* hp, float alpha, void* stream) {
-  if (!d || n < 1 || n > GEMM_GROUP_MAX || (!group && n != 1) || splits < 1 || run < 64)
+  if (!d || n < 1 || n > GEMM_GROUP_MAX || (!group && n != 1) || splits < (group ? 0 : 1) || run < 64)
     return fail(nullptr, LAYUP_ERR_INVALID_ARG, "bad product list");
   Gemm g[GEMM_GROUP_MAX];
   for (int i = 0; i < n; ++i) {

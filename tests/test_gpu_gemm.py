@@ -419,6 +419,7 @@ def _run_error(run):
     (768, 3072, 8192, (2048, 1024, 2752, 2752)),     # splits of 4, 8, 3 and 3
     (1024, 4096, 8192, (4096, 1024, 4096, 4096)),    # 2, 8, 2 and 2
     (2048, 8192, 8192, (8192, 4096, 8192, 8192)),    # enough tiles for whole sums but for the attention projection
+    (1248, 3744, 2880, (2880, 576, 2880, 2880)),     # the same, ragged
 ])
 def test_block_weight_gradients_are_summed_in_short_runs(d, ff, tokens, runs):
     """The four dW products of a block as one group: none is summed in longer
