@@ -1058,7 +1058,7 @@ static const TileCfg kCfgs[kNumCfg] = {
     {256, 128, 1, 0.85f, 1.10f, 3.0f, 1.05f, 1.02f},  // 4x2 waves (each 64x64),  3 stages of K 64
     {128, 192, 1, 0.70f, 0.90f, 3.0f, 1.12f, 1.03f},  // 4x2 waves (each 32x96),  3 stages of K 64
     {128, 128, 2, 0.70f, 1.15f, 3.0f, 1.12f, 1.02f},  // 2x4 waves (each 64x32),  2 stages of K 64
-    {128, 64, 3, 0.41f, 1.10f, 2.5f, 1.12f, 1.05f},   // 2x2 waves (each 64x32),  4 stages of K 32
+    {128, 64, 3, 0.41f, 1.10f, 2.5f, 1.12f, 1.10f},   // 2x2 waves (each 64x32),  4 stages of K 32
     {64, 64, 4, 0.38f, 0.72f, 2.0f, 1.12f, 1.15f},    // 2x2 waves (each 32x32),  2 stages of K 64
 };
 
@@ -1274,7 +1274,7 @@ static Plan choose(const Gemm* g, int n, bool group, bool beside, int only_split
     return tiles;
   };
   auto consider = [&](int c, int sp, int64_t items, float us) {
-    if (beside && limit < g[0].K && (kCfgs[c].occ > 1 || sp > 1 || items > 384)) us *= 1.1f;
+    if (beside && limit < g[0].K && (kCfgs[c].occ > 1 || sp != 1 || items > 384)) us *= 1.1f;
     if (us < best.us) best = Plan{c, sp, limit, us};
   };
   for (int c = 0; c < kNumCfg; ++c) {
