@@ -198,8 +198,9 @@ layup_status layup_refresh_shadow(layup_ctx* ctx);
  * stream (with a separate update stream, the token sort on that stream).
  * Valid only once the previous step's updates are done (the library orders
  * this itself through the streams).  tokens and x are read asynchronously:
- * the caller keeps them allocated and unchanged until the step's work on both streams is done (the compute stream's join
- * at the end of layup_step_ex, or layup_synchronize). */
+ * the caller keeps them allocated and unchanged until the step's work on both
+ * streams is done (the compute stream's join at the end of layup_step_ex, or
+ * layup_synchronize). */
 layup_status layup_forward(layup_ctx* ctx, const int32_t* tokens, const float* x, float* loss_out);
 
 /* Backward pass of one unit (Algorithm 1 "Backward pass at layer l"):
@@ -337,7 +338,7 @@ layup_status layup_step(layup_ctx* ctx, const int32_t* tokens, const float* x,
  * milliseconds from the start of the step's forward pass, from HIP events:
  * forward_ms (host float, nullable) when the forward pass and loss gradient
  * ended; for every unit, ready_ms when its gradient was ready (end of its
- * backward on the compute stream) and applied_ms when its update+mix had
+ * backward, on the stream that ran the last of it) and applied_ms when its update+mix had
  * been applied (end of the launch on the update stream).  applied - ready is
  * the delay with which the unit's update lands, the drift that section 3.2
  * counts per layer; the last ready time minus forward_ms is the backward
@@ -346,9 +347,11 @@ layup_status layup_step(layup_ctx* ctx, const int32_t* tokens, const float* x,
 layup_status layup_unit_timeline(layup_ctx* ctx, float* forward_ms, float* ready_ms, float* applied_ms);
 
 /* GEMM timing of the path: with enable != 0, every later backward of a GPT
- * block brackets each of its linear layers' dX and dW GEMMs (and their
- * split-K sums) with HIP events on the compute stream; enabling or disabling
- * waits for the context and resets the counters.  layup_gemm_timing_read
+ * block brackets each of its linear layers' dX GEMMs (compute stream), and the
+ * one launch of its four dW GEMMs (which also holds the sums of the block's
+ * LayerNorm gradients; update or compute stream), each with its split-K sums,
+ * with HIP events; enabling or disabling waits for the context and resets the
+ * counters.  layup_gemm_timing_read
  * waits for the context and returns the summed GEMM time in milliseconds,
  * the number of timed GEMMs and their algorithmic FLOPs (2 M N K each).  The
  * brackets include each launch's dispatch (a few microseconds per GEMM) and

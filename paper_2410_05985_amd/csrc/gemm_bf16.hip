@@ -898,9 +898,8 @@ __device__ __forceinline__ void splitk_reduce_item(const KArgs& P, int64_t idx) 
   }
 }
 
-template <int EPI>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const KArgs P) {
-  splitk_reduce_item<EPI>(P, (int64_t)blockIdx.x * 256 + threadIdx.x);
+  splitk_reduce_item<EPI_F32>(P, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 template <int EPI>
@@ -917,14 +916,14 @@ hipError_t launch_tiles(const KArgs& P, int batch, hipStream_t s) {
   if (n_log >= (1ll << 31) - 8) return hipErrorInvalidValue;
   dim3 grid((unsigned)((n_log + 7) / 8 * 8));
   constexpr int NT = 64 * WGM * WGN;
-  if constexpr (EPI == EPI_F32 || EPI == EPI_UPDATE) {
+  if constexpr (EPI == EPI_F32) {
     if (P.splits > 1) {
       gemm_bf16_kernel<BM, BN, WGM, WGN, STG, OCC, AK, BKM, EPI, SPLIT_YES, BKV, FL><<<grid, NT, 0, s>>>(P);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
       const int64_t groups = P.M * cdiv(P.N, 4);
       if (groups >= (1ll << 31) * 256ll) return hipErrorInvalidValue;
-      splitk_reduce_kernel<EPI><<<(unsigned)cdiv(groups, 256), 256, 0, s>>>(P);
+      splitk_reduce_kernel<<<(unsigned)cdiv(groups, 256), 256, 0, s>>>(P);
       return hipGetLastError();
     }
   }
@@ -965,11 +964,13 @@ hipError_t dispatch_epi(const Gemm& g, const KArgs& P, hipStream_t s) {
   switch (g.epi) {
     case EPI_F32: return dispatch_layout<BM, BN, WGM, WGN, STG, OCC, BKV, EPI_F32>(g, P, s);
     case EPI_BF16: return dispatch_layout<BM, BN, WGM, WGN, STG, OCC, BKV, EPI_BF16>(g, P, s);
-    case EPI_GELU: return dispatch_layout<BM, BN, WGM, WGN, STG, OCC, BKV, EPI_GELU>(g, P, s);
-    case EPI_UPDATE:  // dW = dY^T X only: both operands m-major
-      if (g.a_kmajor || g.b_kmajor) return hipErrorInvalidValue;
-      return launch_tiles<BM, BN, WGM, WGN, STG, OCC, false, false, EPI_UPDATE, BKV>(P, g.batch, s);
-    default: return dispatch_layout<BM, BN, WGM, WGN, STG, OCC, BKV, EPI_DGELU>(g, P, s);
+    case EPI_GELU:  // forward products
+      if (!g.a_kmajor || !g.b_kmajor) return hipErrorInvalidValue;
+      return launch_tiles<BM, BN, WGM, WGN, STG, OCC, true, true, EPI_GELU, BKV>(P, g.batch, s);
+    case EPI_DGELU:  // dX products
+      if (!g.a_kmajor || g.b_kmajor) return hipErrorInvalidValue;
+      return launch_tiles<BM, BN, WGM, WGN, STG, OCC, true, false, EPI_DGELU, BKV>(P, g.batch, s);
+    default: return hipErrorInvalidValue;  // the weight update: group launches only
   }
 }
 
@@ -1190,7 +1191,7 @@ hipError_t launch_gemm_bf16_cfg(const Gemm& g, int cfg, int splits, int64_t run,
   const int BM = kCfgs[cfg].bm, BN = kCfgs[cfg].bn;
   P.tiles_m = (int)cdiv(g.M, BM);
   P.tiles_n = (int)cdiv(g.N, BN);
-  if (splits > 1 && g.batch == 1 && g.splitk_ws && (g.epi == EPI_F32 || g.epi == EPI_UPDATE) && g.M <= 65535) {
+  if (splits > 1 && g.batch == 1 && g.splitk_ws && g.epi == EPI_F32 && g.M <= 65535) {
     const size_t per_split = (size_t)g.M * g.N * 4 + (g.rowsum ? (size_t)g.M * 4 : 0);
     while (splits > 1 && splits * per_split > g.splitk_ws_bytes) --splits;
     if (splits > 1) {

@@ -151,7 +151,7 @@ struct layup_ctx {
   Layout L;
   layup_buffers buf;
   hipStream_t sc = nullptr, su = nullptr;
-  std::vector<hipEvent_t> ev_unit;     // gradient of unit u ready (compute stream)
+  std::vector<hipEvent_t> ev_unit;     // gradient of unit u ready
   std::vector<hipStream_t> unit_on;    // stream ev_unit was last recorded on
   std::vector<hipEvent_t> ev_applied;  // update+mix of unit u done (update stream)
   hipEvent_t ev_start = nullptr;       // start of the step's forward pass
@@ -956,7 +956,7 @@ layup_status layup_init(layup_ctx** out, const layup_config* cfg, const layup_bu
   c->ev_applied.assign(c->L.n_units, nullptr);
   c->backward_done.assign(c->L.n_units, 0);
   c->unit_on.assign(c->L.n_units, nullptr);
-  // unit events carry timestamps (the per-unit timeline); the join does not
+  // unit events carry timestamps (the per-unit timeline); ev_applied[0] also joins the streams
   for (int u = 0; u < c->L.n_units; ++u) {
     if (hipEventCreate(&c->ev_unit[u]) != hipSuccess || hipEventCreate(&c->ev_applied[u]) != hipSuccess) {
       layup_destroy(c);
