@@ -82,9 +82,8 @@ def test_gemm_split_k_deterministic(layout):
 
 @pytest.mark.parametrize("layout", ["kn", "kk"])
 def test_gemm_long_k_split(layout):
-    """K >= 16384 with a float32 output (the tied head's dX over the
-    vocabulary) takes the 256x256 tile with an 8-way split of K; ragged M, N
-    and K, reproducible bit for bit."""
+    """K >= 16384 with a float32 output (as the tied head's dX over the
+    vocabulary): a split of K, ragged M, N and K, reproducible bit for bit."""
     a, ref = run(layout, 520, 264, 16400, ws=True, seed=13)
     b, _ = run(layout, 520, 264, 16400, ws=True, seed=13)
     compare(a, ref, 2e-2, "long-K split")
@@ -140,8 +139,8 @@ def test_gemm_degenerate_sizes(layout):
 
 
 def test_gemm_dw_many_tiles():
-    """dW = dY^T X with at least 512 output tiles (the head's dW) takes the
-    256x128 tile; ragged N and K."""
+    """dW = dY^T X with more output tiles than CUs (as the head's dW); ragged N
+    and K."""
     got, ref = run("mn", 4096, 2200, 200, seed=17)
     compare(got, ref, 2e-2, "dW many tiles")
     assert np.linalg.norm(got - ref) <= 1e-4 * np.linalg.norm(ref)
@@ -302,9 +301,10 @@ def test_gemm_f32_large_tiles(ak, bk, M, N, K, ld):
 @pytest.mark.parametrize("M,N", [(8192, 768), (8192, 3072), (4104, 4096), (2048, 8192), (1368, 3304), (520, 264), (72, 40)])
 @pytest.mark.parametrize("K", [8, 64, 72, 128, 200, 264])
 def test_gemm_tiles_and_short_k(layout, M, N, K):
-    """Every tile configuration (the choice goes by the sizes) at the edges of
-    its pipeline: fewer K steps than stages, exactly as many, one more, and
-    partial last steps.  Bound per element: a float32 sum of K exact products
+    """The tiles the library chooses for large and small outputs with a short K
+    (test_gemm_every_tile names them all) at the edges of their pipelines:
+    fewer K steps than stages, exactly as many, one more, and partial last
+    steps.  Bound per element: a float32 sum of K exact products
     in any order, 2 (K + 8) 2^-24 of the sum of absolute values (the factor
     two covers adders that truncate)."""
     ak, bk = {"kk": (True, True), "kn": (True, False), "mn": (False, False)}[layout]
@@ -442,3 +442,92 @@ def test_long_products_are_summed_in_short_runs(layout, M, N, K, run):
     LU.layup_gemm_bf16(p.desc, torch.cuda.current_stream())
     torch.cuda.synchronize()
     assert p.rel() <= _run_error(run), p.rel()
+
+
+def _within(p, tail=8):
+    """C and the row sums within a float32 sum of K exact products in any
+    order: 2 (K + 8) 2^-24 of the sum of absolute values (the factor two
+    covers adders that truncate)."""
+    K = p.a.shape[1]
+    a, b = p.a.double(), p.b.double()
+    eps = 2 * (K + tail) * 2.0 ** -24
+    assert torch.all((p.C.double() - a @ b).abs() <= eps * (a.abs() @ b.abs()))
+    if p.rs is not None:
+        assert torch.all((p.rs.double() - a.sum(1)).abs() <= eps * a.abs().sum(1))
+
+
+# (K, split, longest run): no whole K step, one, as many as stages and one more, partial last steps; splits whose
+# length is an odd multiple of 32 (1000 / 2 -> 512, 1056 / 3 -> 352, 4576 / 5 -> 928, with the last one short); runs of
+# one K step, of some, longer than the split
+EDGES = [(8, 1, None), (64, 1, None), (72, 1, None), (192, 1, None), (264, 1, 64), (328, 1, 128), (1000, 2, None),
+         (1056, 3, None), (1056, 3, 64), (4576, 5, 512), (4576, 1, 512), (2056, 1, 1984)]
+
+
+@pytest.mark.parametrize("cfg", range(7))
+@pytest.mark.parametrize("layout", ["kk", "kn", "mn"])
+def test_gemm_every_tile(layout, cfg):
+    """Every tile configuration in every layout, two tiles and a ragged rest in
+    both dimensions, at the edges of the K loop, of the split of K and of the
+    runs that the accumulators take (tiles that have the short-run form)."""
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device=DEV)
+    flushes = cfg >= 2 and not (cfg == 4 and layout != "mn")
+    for K, splits, run in EDGES:
+        if run is not None and not flushes:
+            continue
+        p = _Prod(layout, 544, 536, K, ws, seed=cfg)
+        _tile([p.desc], cfg=cfg, splits=splits, run=run or 1 << 62)
+        _within(p)
+
+
+@pytest.mark.parametrize("cfg", [0, 2, 4])
+@pytest.mark.parametrize("K,splits", [(8, 1), (200, 1), (1000, 2), (4576, 5), (2056, 1), (1600, 0), (2624, 0)])
+def test_gemm_group_every_tile(cfg, K, splits):
+    """Four products of a group, small and ragged, on each of its tiles: without
+    a split, split alike, and each as far as its limit asks (splits = 0: from
+    K = 1536 on)."""
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device=DEV)
+    ps = [_Prod("mn", m, n, K, ws, seed=cfg) for m, n in ((264, 136), (72, 72), (520, 264), (2048, 2304))]
+    _tile([p.desc for p in ps], group=1, cfg=cfg, splits=splits)
+    for p in ps:
+        _within(p)
+
+
+@pytest.mark.parametrize("cfg", [0, 2, 4])
+@pytest.mark.parametrize("K,splits", [(72, 1), (1000, 2), (2056, 1), (1600, 0)])
+@pytest.mark.parametrize("optim", ["adamw", "sgd"])
+def test_gemm_group_update_epilogue(cfg, K, splits, optim):
+    """The same with the weight update in the epilogue or in the split's sum: equal to the gradients of the float32 epilogue
+    put through the update + mix kernel, bit for bit but for the last rounding
+    of the update (2 2^-24 of the step's terms)."""
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device=DEV)
+    hp = LU.hparams("adamw", 1e-2, 0.0, 0.1, 0.9, 0.95, 1e-8, 3) if optim == "adamw" else LU.hparams("sgd", 1e-2, 0.9, 5e-5)
+    ps = [_Prod("mn", m, n, K, ws, seed=cfg) for m, n in ((264, 136), (72, 72), (520, 264))]
+    _tile([p.desc for p in ps], group=1, cfg=cfg, splits=splits)
+    g = torch.Generator(device=DEV).manual_seed(K)
+    fused, plain, ups = [], [], []
+    for p in ps:
+        n = p.C.numel()
+        st = {k: torch.randn(n, device=DEV, generator=g) for k in ("param", "state0", "peer")}
+        st["state1"] = torch.rand(n, device=DEV, generator=g)
+        pair = [{k: v.clone() for k, v in st.items()} for _ in range(2)]
+        for d in pair:
+            d["param_bf16"] = torch.zeros(n, dtype=torch.int16, device=DEV)
+        ts = []
+        for d in pair:
+            t = LU.layup_tensor()
+            t.param, t.state0, t.peer = (d[k].data_ptr() for k in ("param", "state0", "peer"))
+            t.state1 = d["state1"].data_ptr() if optim == "adamw" else None
+            t.param_bf16, t.numel, t.decay, t.grad = d["param_bf16"].data_ptr(), n, 1, p.C.data_ptr()
+            ts.append(t)
+        fused.append(pair[0])
+        plain.append(pair[1])
+        ups.append(ts[0])
+        LU.layup_layer_update_mix_static([ts[1]], hp, 0.25, None, torch.cuda.current_stream())
+    keep = [p.rs.clone() for p in ps]
+    _tile([p.desc for p in ps], group=1, cfg=cfg, splits=splits, upd=ups, hp=hp, alpha=0.25)
+    for p, rs, a, b in zip(ps, keep, fused, plain):
+        assert torch.equal(p.rs, rs)
+        for k in ("param", "state0", "state1"):
+            assert torch.all((a[k] - b[k]).abs() <= 2.0 ** -22 * (1 + b[k].abs())), k
+        assert torch.equal(a["peer"], b["peer"])
+        assert torch.equal(a["param_bf16"].view(torch.bfloat16), a["param"].to(torch.bfloat16))

@@ -139,6 +139,19 @@ def test_mlp_cross_entropy_rows_and_classes(batch, classes):
     mlp_one_step((24, classes), batch)
 
 
+@pytest.mark.parametrize("two_streams", [True, False])
+@pytest.mark.parametrize("dims,batch", [
+    ((37, 19, 33, 7), 5), ((37, 19, 33, 7), 65), ((9, 16, 1), 3),   # dW and dX in one launch, ragged
+    ((2048, 1030, 1021, 37), 70),   # too large for one launch: 32 x 32 tiles, four waves and one
+    ((2048, 2052, 130, 12), 260),   # 64 x 64 tiles: dW with its bias sums;
+    ((300, 2052, 300, 12), 2080),   # the forward with ReLU and dX with its mask
+])
+def test_mlp_widths(dims, batch, two_streams):
+    """The float32 product's forms in a training step: fused bias sums, ReLU
+    and ReLU gradient on every tile size."""
+    mlp_one_step(dims, batch, two_streams)
+
+
 # ------------------------------------------------------------------ GPT
 
 def check_adamw_params(got, ref, m_gpu, g_ref, cfg, name):
@@ -473,7 +486,7 @@ def test_gemm_timing_counts_the_block_backward_gemms():
     m.close()
 
 
-@pytest.mark.parametrize("cfg", [S.GPT_TEST, S.GPT_TEST_LONG], ids=lambda c: c.name)
+@pytest.mark.parametrize("cfg", [S.GPT_TEST, S.GPT_TEST_LONG, S.GPT2_SMALL_2L, S.GPT_TEST_W2048], ids=lambda c: c.name)
 def test_fused_dw_schedule_matches_oracle(cfg):
     """The fused schedule (each block's weight matrices updated and mixed by
     their dW GEMM, in its epilogue or, with 2048 tokens, in its split-K sum):
