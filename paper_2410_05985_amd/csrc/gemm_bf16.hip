@@ -662,8 +662,7 @@ __device__ __forceinline__ void gemm_item(const KArgs& P, int lid) {
   int kt = 0, slot = 0;
   const int run = FL ? (int)min(P.run / BKV, (int64_t)1 << 30) : 0;  // K steps
   int left = run;
-  for (; kt + S - 1 < n_full; ++kt) {
-    k_step(IntC<1>{}, kt, slot);
+  auto end_step = [&]() {
     slot = slot + 1 == S ? 0 : slot + 1;
     if constexpr (FL) {
       if (--left == 0) {
@@ -671,10 +670,14 @@ __device__ __forceinline__ void gemm_item(const KArgs& P, int lid) {
         left = run;
       }
     }
+  };
+  for (; kt + S - 1 < n_full; ++kt) {
+    k_step(IntC<1>{}, kt, slot);
+    end_step();
   }
   for (; kt < nk; ++kt) {
     k_step(IntC<0>{}, kt, slot);
-    slot = slot + 1 == S ? 0 : slot + 1;
+    end_step();
   }
   multiply(IntC<1>{}, IntC<0>{}, 0);
   if constexpr (FL) {

@@ -492,6 +492,21 @@ def test_gemm_group_every_tile(cfg, K, splits):
         _within(p)
 
 
+@pytest.mark.parametrize("K", [1600, 2112, 2624, 2632, 3136, 4672])
+def test_gemm_group_tiles_agree_bit_for_bit(K):
+    """The tile does not change the order of the sums: 256 x 128 and 128 x 128,
+    with rings of three and of two stages, give the same bits, also where a run
+    ends within the last steps of K (2624 is 41 steps in runs of 8)."""
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device=DEV)
+    ps = [_Prod("mn", m, n, K, ws) for m, n in ((264, 136), (72, 72), (520, 264))]
+    out = []
+    for cfg in (2, 4):
+        _tile([p.desc for p in ps], group=1, cfg=cfg)
+        out.append([t.clone() for p in ps for t in (p.C, p.rs)])
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("cfg", [0, 2, 4])
 @pytest.mark.parametrize("K,splits", [(72, 1), (1000, 2), (2056, 1), (1600, 0)])
 @pytest.mark.parametrize("optim", ["adamw", "sgd"])
