@@ -27,7 +27,7 @@ Other workloads (one JSON line each, not the default bench line):
                            this library's GEMM and with torch.matmul
                            (hipBLASLt) on the same operands, cold operands
   --workload kernels       one launch each of: a 1 GiB copy (counter
-                           calibration), one GPT-2-small block's 8 backward
+                           calibration), one GPT-2-small block's backward
                            GEMMs, one block's update+mix -- for rocprofv3 --pmc
 
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu-baseline]
@@ -135,6 +135,53 @@ def time_gemms(torch, LU, shapes, reps, stream, cold_bytes=512 << 20):
                         tflops=2.0 * M * N * K / (ms * 1e-3) / 1e12))
         del bufs, descs
     return res
+
+
+def block_dw_launch(LU, descs, stream):
+    """A block's dW GEMMs as the two-stream step launches them: one group, the
+    tile and split the library chooses beside the dX chain (through the
+    library's test entry; the LayerNorm sums that ride along in the step are
+    left out)."""
+    import ctypes
+    f = LU.lib().layup_test_gemm_tile
+    f.argtypes = [ctypes.c_void_p] + [ctypes.c_int32] * 4 + [ctypes.c_int64] + [ctypes.c_void_p] * 2 + \
+        [ctypes.c_float, ctypes.c_void_p]
+    arr = (LU.layup_gemm_desc * len(descs))(*descs)
+
+    def launch():
+        if f(ctypes.addressof(arr), len(descs), 2, -1, 1, 1 << 62, None, None, 0.5, stream.cuda_stream):
+            raise SystemExit(LU.lib().layup_global_error().decode())
+    return launch
+
+
+def time_block_dw(torch, LU, shapes, reps, stream, cold_bytes=512 << 20):
+    """Average duration of that launch (with its split-K sums and bias
+    gradients), timed as in time_gemms."""
+    ws = torch.empty(128 << 20, dtype=torch.uint8, device="cuda")
+    per = sum(2 * M * K + 2 * N * K + 4 * M * N for _, M, N, K, _, _ in shapes)
+    R = max(1, min(16, -(-cold_bytes // per)))
+    bufs, launches = [], []
+    for _ in range(R):
+        descs = []
+        for _, M, N, K, _, _ in shapes:
+            A = torch.randn((K, M), device="cuda").to(torch.bfloat16)
+            B = torch.randn((K, N), device="cuda").to(torch.bfloat16)
+            C, rs = torch.empty((M, N), device="cuda"), torch.empty(M, device="cuda")
+            bufs.append((A, B, C, rs))
+            descs.append(LU.gemm_desc(A, B, C, M, N, K, M, N, N, False, False, True, workspace=ws,
+                                      workspace_bytes=ws.numel(), a_rowsum=rs))
+        launches.append(block_dw_launch(LU, descs, stream))
+    torch.cuda.synchronize()
+    for f in launches:
+        f()
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record(stream)
+    for r in range(reps):
+        launches[r % R]()
+    e1.record(stream)
+    e1.synchronize()
+    ms = e0.elapsed_time(e1) / reps
+    return dict(name="block.dW", ms=ms, tflops=sum(2.0 * M * N * K for _, M, N, K, _, _ in shapes) / (ms * 1e-3) / 1e12)
 
 
 def time_update_mix(torch, LU, m, units, hp, alpha, reps, stream):
@@ -570,22 +617,26 @@ def bench_gemm_yardstick(args, torch, LU, S):
 
 def bench_kernels(args, torch, LU, S):
     """Single launches for hardware-counter runs, in this order: a 1 GiB
-    device copy (known traffic: 1 GiB read + 1 GiB written), the 8 backward
-    GEMMs of one GPT-2-small block (qkv, proj, fc, mproj; dX then dW), the
-    update+mix of one GPT-2-small block (AdamW + bf16 copy).  The device is
+    device copy (known traffic: 1 GiB read + 1 GiB written), the four dX GEMMs
+    of one GPT-2-small block (qkv, proj, fc, mproj), its four dW GEMMs in one
+    launch, the update+mix of one GPT-2-small block (AdamW + bf16 copy).  The device is
     synchronised between launches so each dispatch stands alone."""
     cfg = S.GPT2_SMALL
     src = torch.ones(1 << 28, dtype=torch.float32, device="cuda")
     dst = torch.empty_like(src)
     blk, _ = backward_gemm_shapes(cfg)
     ops = []
-    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(256 << 20, dtype=torch.uint8, device="cuda")
+    dws = []
     for name, M, N, K, ak, bk in blk:
         A = torch.randn((M, K) if ak else (K, M), device="cuda").to(torch.bfloat16)
         B = torch.randn((N, K) if bk else (K, N), device="cuda").to(torch.bfloat16)
         C = torch.empty((M, N), dtype=torch.float32, device="cuda")
-        ops.append((name, LU.gemm_desc(A, B, C, M, N, K, K if ak else M, K if bk else N, N, ak, bk, True,
-                                       workspace=ws, workspace_bytes=64 << 20), (A, B, C)))
+        rs = None if ak else torch.empty(M, device="cuda")
+        room = (256 if ak else 128) << 20  # as in the step: 256 MB on the compute stream, 128 MB beside it
+        d = LU.gemm_desc(A, B, C, M, N, K, K if ak else M, K if bk else N, N, ak, bk, True,
+                         workspace=ws, workspace_bytes=room, a_rowsum=rs)
+        (ops if ak else dws).append((name, d, (A, B, C, rs)))
     n = 7_087_872
     bufs = [torch.randn(n, device="cuda") * 1e-3 for _ in range(5)]
     p16 = torch.zeros(n, dtype=torch.int16, device="cuda")
@@ -601,12 +652,14 @@ def bench_kernels(args, torch, LU, S):
     for name, d, _ in ops:
         LU.layup_gemm_bf16(d, torch.cuda.current_stream())
         torch.cuda.synchronize()
+    block_dw_launch(LU, [d for _, d, _ in dws], torch.cuda.current_stream())()
+    torch.cuda.synchronize()
     flush.add_(1.0)
     torch.cuda.synchronize()
     LU.layup_layer_update_mix(None, [t], hp, cfg.alpha, stream=torch.cuda.current_stream())
     torch.cuda.synchronize()
     print(json.dumps({"workload": "kernels", "copy_bytes": 2 * src.numel() * 4,
-                      "gemms": [o[0] for o in ops], "update_mix_numel": n,
+                      "gemms": [o[0] for o in ops] + ["block.dW"], "update_mix_numel": n,
                       "update_mix_algorithmic_bytes": 34 * n}), flush=True)
 
 
@@ -614,9 +667,9 @@ def pmc_summary(fetch_csv, write_csv):
     """HBM bytes of the kernels of `bench.py --workload kernels` from two
     counter passes.  The 1 GiB device copy calibrates the counters (it reads
     and writes 1 GiB): fetch and write counts are scaled so that the copy
-    reads and writes exactly that.  The dispatches after the copy are the 8
-    backward GEMMs of a GPT-2-small block (each with its split-K reduction,
-    if any), then the block's update+mix."""
+    reads and writes exactly that.  The dispatches after the copy are the four
+    dX GEMMs of a GPT-2-small block and its dW launch (each with its split-K
+    reduction, if any), then the block's update+mix."""
     import csv
 
     def load(path, counter):
@@ -635,17 +688,17 @@ def pmc_summary(fetch_csv, write_csv):
     ci = next(i for i, n in enumerate(names) if "copyBuffer" in n)
     gib = float(1 << 30)
     ff, wf = gib / (f[ci][1] * 1024), gib / (w[ci][1] * 1024)
-    gemm_names = ["qkv.dX", "qkv.dW", "proj.dX", "proj.dW", "fc.dX", "fc.dW", "mproj.dX", "mproj.dW"]
+    gemm_names = ["qkv.dX", "proj.dX", "fc.dX", "mproj.dX", "block.dW"]
     groups, um = [], None
     for i in range(ci + 1, len(names)):
-        if "gemm_bf16_kernel" in names[i]:
+        if "gemm_bf16_kernel" in names[i] or "gemm_bf16_group_kernel" in names[i]:
             groups.append([i])
         elif "splitk_reduce" in names[i]:
             groups[-1].append(i)
         elif "update_mix_kernel" in names[i]:
             um = i
             break
-    assert len(groups) == 8 and um is not None, [names[g[0]][:40] for g in groups]
+    assert len(groups) == len(gemm_names) and um is not None, [names[g[0]][:40] for g in groups]
     sha = lambda src: hashlib.sha256(open(os.path.join(ROOT, "paper_2410_05985_amd", "csrc", src), "rb")
                                      .read()).hexdigest()[:16]
     per, tot = [], 0.0
@@ -871,7 +924,9 @@ def main():
     ks = torch.cuda.Stream()
     blk, head = backward_gemm_shapes(cfg)
     g = time_gemms(torch, LU, blk + head, args.kernel_reps, ks)
-    blk_ms = sum(x["ms"] for x in g[:len(blk)])
+    # the block's dX GEMMs, a launch each, and its dW GEMMs in one, as in the step
+    dw = time_block_dw(torch, LU, [x for x in blk if x[0].endswith("dW")], args.kernel_reps, ks)
+    blk_ms = sum(x["ms"] for x in g[:len(blk)] if x["name"].endswith("dX")) + dw["ms"]
     blk_flops = sum(2.0 * x["M"] * x["N"] * x["K"] for x in g[:len(blk)])
     gemm_tflops = blk_flops / (blk_ms * 1e-3) / 1e12
     um = time_update_mix(torch, LU, model, range(1, cfg.n_layer + 1), hp, cfg.alpha, args.kernel_reps, ks)
@@ -883,6 +938,8 @@ def main():
     for x in g:
         print(f"[bench] gemm {x['name']:9s} {x['M']}x{x['N']}x{x['K']}: {x['ms']*1e3:8.1f} us "
               f"{x['tflops']:7.1f} TFLOP/s", file=sys.stderr, flush=True)
+    print(f"[bench] gemm {dw['name']:9s} (four products, one launch): {dw['ms']*1e3:8.1f} us {dw['tflops']:7.1f} TFLOP/s",
+          file=sys.stderr, flush=True)
     print(f"[bench] update+mix block unit: {um['ms']*1e3:.1f} us {um['gbs']:.0f} GB/s",
           file=sys.stderr, flush=True)
 
@@ -891,7 +948,8 @@ def main():
     roofline = dict(bound="mfma", achieved=round(gemm_tflops, 2), peak=PEAK_BF16_TFLOPS,
                     unit="TFLOP/s", frac=round(gemm_tflops / PEAK_BF16_TFLOPS, 4),
                     traffic=traffic,
-                    kernel="gemm_bf16_kernel (a block's 8 backward dX/dW GEMMs + split-K sums, operands from HBM)",
+                    kernel="gemm_bf16_kernel, gemm_bf16_group_kernel (a block's 4 dX GEMMs and its 4 dW GEMMs in one "
+                           "launch, operands from HBM)",
                     algorithmic_flops_per_block=blk_flops,
                     launch_ms_per_block=round(blk_ms, 5))
     out = {
