@@ -96,7 +96,7 @@ LISTING = """0000000000000100 <kernel>:
 
 @pytest.mark.parametrize("n,early,bad", [(1, 7, set()), (0, 11, set()), (1, 9, {0x118}), (2, 1, {0x11c}),
                                          (2, 5, {0x118, 0x11c})])
-def test_checker_finds_a_read_before_its_wait(n, early, bad):
+def test_a_read_before_its_wait_is_found(n, early, bad):
     ins = _functions(LISTING.format(n=n, early=early).splitlines())["kernel"]
     assert len(ins) == 7
     assert touched_in_flight(ins) == bad
